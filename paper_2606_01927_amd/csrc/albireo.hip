@@ -30,6 +30,7 @@
 #include <utility>
 
 #include "albireo.h"
+#include "penalties.h"
 #include "stream.h"
 
 namespace {
@@ -2568,17 +2569,7 @@ __global__ __launch_bounds__(NT) void k_sample_multi(KArgs a) {
 
 }  // namespace
 
-// ==============================================================================================
-// Standalone penalties: albireo_apply_penalties.  A workgroup handles one tile of one row: every id of
-// the row's output history, prompt history or penalty state that falls in the tile is folded into a
-// 32-bit word per tile element in LDS (bits 0-30 the output count, bit 31 the prompt mark: the penalty
-// state's encoding), and the tile is streamed to the fp32 output (each element read and written by the
-// same thread, so the output may alias an fp32 input).  The words are exact for any history length.
-// ==============================================================================================
 namespace {
-
-constexpr int PEN_NT = 256;
-constexpr int64_t PEN_TILE = 16384;  // elements per workgroup (64 KB of LDS words)
 
 // The uniforms alone (one thread per row), for callers that sample elsewhere.
 __global__ __launch_bounds__(256) void k_philox_uniforms(uint64_t seed, uint64_t step, const int64_t* seq_ids,
@@ -2602,77 +2593,6 @@ __global__ __launch_bounds__(256) void k_backfill(const int32_t* ids, const int3
 __global__ __launch_bounds__(256) void k_zero16(uint4* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
     p[i] = make_uint4(0, 0, 0, 0);
-}
-
-// The prompt history (repetition only) and the per-sequence penalty state, beside the output history.
-struct PenExtra {
-  const int64_t* prompt_offsets;
-  const int32_t* prompt_ids;
-  int64_t prompt_len;
-  const int32_t* st_ids;
-  const uint32_t* st_counts;
-  const int32_t* st_len;
-  int32_t st_cap;
-};
-
-template <class DT>
-__global__ __launch_bounds__(PEN_NT) void k_penalties(const unsigned char* logits, int64_t V, int64_t ld,
-                                                      DevParams prm, PenExtra ex, float* out) {
-  __shared__ uint32_t cvs[PEN_TILE];
-  const int64_t row = blockIdx.y;
-  const int64_t t0 = (int64_t)blockIdx.x * PEN_TILE;
-  const int64_t t1 = min(V, t0 + PEN_TILE);
-  const unsigned char* rowp = logits + row * ld * DT::ES;
-  float rep = prm.rep ? prm.rep[row] : 1.0f;
-  float freq = prm.freq ? prm.freq[row] : 0.0f;
-  float pres = prm.pres ? prm.pres[row] : 0.0f;
-  if (!(rep > 0.0f) || isinf(rep)) rep = 1.0f;
-  if (!isfinite(freq)) freq = 0.0f;
-  if (!isfinite(pres)) pres = 0.0f;
-  int64_t lo = 0, hi = 0;
-  if (prm.hist_offsets) {
-    lo = prm.hist_offsets[row];
-    hi = prm.hist_offsets[row + 1];
-    if (lo < 0 || hi < lo || hi > prm.hist_len) lo = hi = 0;
-  }
-  int64_t plo = 0, phi = 0;
-  if (ex.prompt_offsets) {
-    plo = ex.prompt_offsets[row];
-    phi = ex.prompt_offsets[row + 1];
-    if (plo < 0 || phi < plo || phi > ex.prompt_len) plo = phi = 0;
-  }
-  int sn = 0;
-  if (ex.st_len) {
-    sn = ex.st_len[row];
-    sn = sn < 0 ? 0 : (sn > ex.st_cap ? ex.st_cap : sn);
-  }
-  const bool pen = hi > lo || phi > plo || sn > 0;
-  if (pen) {
-    for (int i = threadIdx.x; i < PEN_TILE; i += PEN_NT) cvs[i] = 0;
-    __syncthreads();
-    for (int64_t h = lo + threadIdx.x; h < hi; h += PEN_NT) {
-      const int id = prm.hist_ids[h];
-      if (id >= t0 && id < t1) atomicAdd(&cvs[id - t0], 1u);
-    }
-    for (int64_t h = plo + threadIdx.x; h < phi; h += PEN_NT) {
-      const int id = ex.prompt_ids[h];
-      if (id >= t0 && id < t1) atomicOr(&cvs[id - t0], 0x80000000u);
-    }
-    for (int e = threadIdx.x; e < sn; e += PEN_NT) {
-      const int id = ex.st_ids[row * ex.st_cap + e];
-      if (id >= t0 && id < t1) cvs[id - t0] = ex.st_counts[row * ex.st_cap + e];  // distinct ids
-    }
-    __syncthreads();
-  }
-  float* orow = out + row * V;
-  for (int64_t i = t0 + threadIdx.x; i < t1; i += PEN_NT) {
-    float x = DT::load1(rowp, i);
-    if (pen) {
-      const uint32_t cv = cvs[i - t0];
-      if (cv != 0) x = penalise_cv(x, cv, rep, freq, pres);
-    }
-    orow[i] = x;
-  }
 }
 
 // ==============================================================================================
@@ -3202,28 +3122,7 @@ albireo_status_t albireo_apply_penalties(const void* logits, albireo_dtype_t dty
   // aliasing is only defined for an fp32 input with ld == V (element-wise in place)
   if (static_cast<const void*>(out_logits) == logits && !(dtype == ALBIREO_F32 && ld == V)) return ALBIREO_E_INVALID;
   if (B > 65535) return ALBIREO_E_UNSUPPORTED;
-  const DevParams d = dev_params(params);
-  PenExtra ex;
-  memset(&ex, 0, sizeof ex);
-  if (params) {
-    ex.prompt_offsets = params->prompt_offsets;
-    ex.prompt_ids = params->prompt_ids;
-    ex.prompt_len = params->prompt_len;
-    if (params->state) {
-      ex.st_ids = params->state->ids;
-      ex.st_counts = params->state->counts;
-      ex.st_len = params->state->len;
-      ex.st_cap = params->state->cap;
-    }
-  }
-  const dim3 grid((unsigned)((V + PEN_TILE - 1) / PEN_TILE), (unsigned)B);
-  if (dtype == ALBIREO_BF16)
-    hipLaunchKernelGGL(k_penalties<BF16T>, grid, dim3(PEN_NT), 0, stream,
-                       static_cast<const unsigned char*>(logits), V, ld, d, ex, out_logits);
-  else
-    hipLaunchKernelGGL(k_penalties<F32T>, grid, dim3(PEN_NT), 0, stream,
-                       static_cast<const unsigned char*>(logits), V, ld, d, ex, out_logits);
-  return hipGetLastError() == hipSuccess ? ALBIREO_OK : ALBIREO_E_LAUNCH;
+  return albireo_penalties::launch(logits, dtype, B, V, ld, params, out_logits, stream);
 }
 
 const char* albireo_status_string(albireo_status_t s) {
