@@ -9,6 +9,8 @@
 
 #include <stdint.h>
 
+#include <mutex>
+
 #include "albireo.h"
 
 namespace {
@@ -34,7 +36,112 @@ __device__ __forceinline__ void csr_row(const int64_t* off, int64_t len, int64_t
   hi = b;
 }
 
-// One workgroup per row: the row's occurrences become keys 2 id + (1 for a prompt occurrence), sorted in
+// One workgroup per row, vocabularies of up to BM_MAXV ids: a presence bitmap of the vocabulary in LDS
+// takes every occurrence's id, a prefix count over its words numbers the distinct ids in ascending
+// order, and every occurrence then counts itself at its id's number.  Nothing is sorted.
+//
+// Bound: the latency of the row's two round trips to memory and eight barriers, about 4096 LDS atomics
+// on the way; one workgroup per CU (up to 136 KB of LDS).  64 rows of 1000 + 3000 ids, V = 128256:
+// 50.9 us with the bitonic sort below (78 barrier-separated stages over 4096 keys), 8.9 us here.
+constexpr int64_t BM_MAXV = 393216;       // 48 KB of bitmap and 24 KB of word prefixes beside 64 KB of entries
+
+__global__ __launch_bounds__(INIT_NT) void k_state_init_bitmap(albireo_penalty_state_t st, int64_t V, int nwords,
+                                                               const int64_t* p_off, const int32_t* p_ids,
+                                                               int64_t p_len, const int64_t* o_off,
+                                                               const int32_t* o_ids, int64_t o_len) {
+  extern __shared__ __align__(16) uint32_t smem[];
+  uint32_t* cnt = smem;                                       // [MAXS] per distinct id: count and prompt mark
+  int32_t* idl = reinterpret_cast<int32_t*>(smem + MAXS);     // [MAXS] the ids themselves
+  uint32_t* bitmap = smem + 2 * MAXS;                         // [nwords], a multiple of four words
+  uint16_t* wpref = reinterpret_cast<uint16_t*>(bitmap + nwords);  // distinct ids before each word
+  __shared__ uint32_t part[INIT_NT / 64];
+  __shared__ uint32_t sflags;
+  const int t = threadIdx.x;
+  const int64_t row = blockIdx.x;
+  uint32_t flags = 0;
+  int64_t plo, phi, olo, ohi;
+  csr_row(p_off, p_len, row, plo, phi, flags);
+  csr_row(o_off, o_len, row, olo, ohi, flags);
+  const int64_t np = phi - plo, no = ohi - olo;
+  int64_t total = np + no;
+  if (total > MAXS) {
+    flags |= ALBIREO_FLAG_LIMIT;
+    total = MAXS;
+  }
+  const int n = (int)total;
+  // this thread's occurrences, all in flight together (prompt first, as the cut at MAXS takes them; an
+  // index past the row's end reloads its first occurrence)
+  int32_t id[IPT];
+  if (n > 0) {
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      const int j = t + q * INIT_NT < n ? t + q * INIT_NT : 0;
+      id[q] = *(j < np ? p_ids + plo + j : o_ids + olo + (j - np));
+    }
+  }
+  if (t == 0) sflags = flags;
+  for (int i = t; i < nwords / 4; i += INIT_NT) reinterpret_cast<uint4*>(bitmap)[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = t; i < MAXS / 4; i += INIT_NT) reinterpret_cast<uint4*>(cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  uint32_t bad = 0;
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    if (t + q * INIT_NT < n) {
+      if (id[q] >= 0 && (int64_t)id[q] < V) atomicOr(&bitmap[id[q] >> 5], 1u << (id[q] & 31));
+      else bad = 1;
+    }
+  }
+  if (bad) atomicOr(&sflags, ALBIREO_FLAG_BAD_INPUT);
+  __syncthreads();
+  // word prefixes: thread t owns wpt consecutive words
+  const int wpt = (nwords + INIT_NT - 1) / INIT_NT;
+  const int w0 = min(t * wpt, nwords), w1 = min(w0 + wpt, nwords);
+  int loc = 0;
+  for (int w = w0; w < w1; ++w) loc += __popc(bitmap[w]);
+  const int l = t & 63, wv = t >> 6;
+  int incl = loc;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if (l >= o) incl += v;
+  }
+  if (l == 63) part[wv] = (uint32_t)incl;
+  __syncthreads();
+  int ex = incl - loc, nd = 0;
+  for (int q = 0; q < INIT_NT / 64; ++q) {
+    if (q < wv) ex += (int)part[q];
+    nd += (int)part[q];
+  }
+  for (int w = w0; w < w1; ++w) {
+    wpref[w] = (uint16_t)ex;  // at most MAXS distinct ids
+    ex += __popc(bitmap[w]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    const int j = t + q * INIT_NT;
+    if (j < n && id[q] >= 0 && (int64_t)id[q] < V) {
+      const int w = id[q] >> 5;
+      const int rank = (int)wpref[w] + __popc(bitmap[w] & ((1u << (id[q] & 31)) - 1u));
+      idl[rank] = id[q];  // every occurrence of the id writes the same value
+      if (j < np) atomicOr(&cnt[rank], TAG_PROMPT);
+      else atomicAdd(&cnt[rank], 1u);
+    }
+  }
+  __syncthreads();
+  const int keep = min(nd, st.cap);  // the smallest ids
+  int32_t* ids = st.ids + row * st.cap;
+  uint32_t* counts = st.counts + row * st.cap;
+  for (int d = t; d < keep; d += INIT_NT) {
+    ids[d] = idl[d];
+    counts[d] = cnt[d];
+  }
+  if (t == 0) {
+    st.len[row] = keep;
+    st.flags[row] = sflags | (nd > st.cap ? ALBIREO_FLAG_LIMIT : 0u);
+  }
+}
+
+// Wider vocabularies: one workgroup per row, the row's occurrences become keys 2 id + (1 for a prompt occurrence), sorted in
 // LDS (ascending id, output occurrences before prompt ones), and every run of one id becomes an entry
 // whose count is the number of output occurrences in the run and whose prompt mark is the tag of its
 // last key.
@@ -230,6 +337,22 @@ __global__ __launch_bounds__(APP_NT) void k_state_append(albireo_penalty_state_t
   }
 }
 
+// k_state_init_bitmap's dynamic LDS passes 64 KB: allowed once per device.
+constexpr int MAX_DEV = 64;
+bool big_lds_allowed() {
+  static std::mutex mu;
+  static bool done[MAX_DEV];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEV) return false;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!done[dev]) {
+    const int most = (int)(MAXS * 8 + BM_MAXV / 32 * 6);
+    done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_state_init_bitmap),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess;
+  }
+  return done[dev];
+}
+
 albireo_status_t check_state(const albireo_penalty_state_t* st, int64_t B, int64_t V) {
   if (!st || B < 0 || V <= 0) return ALBIREO_E_INVALID;
   if (V >= ((int64_t)1 << 31) - 16 || B > 0x7fffffff) return ALBIREO_E_UNSUPPORTED;
@@ -251,6 +374,14 @@ albireo_status_t albireo_penalty_state_init(const albireo_penalty_state_t* state
   if (prompt_offsets && (prompt_len < 0 || (prompt_len > 0 && !prompt_ids))) return ALBIREO_E_INVALID;
   if (out_offsets && (out_len < 0 || (out_len > 0 && !out_ids))) return ALBIREO_E_INVALID;
   if (B == 0) return ALBIREO_OK;
+  if (V <= BM_MAXV) {
+    const int nwords = (int)((V + 127) / 128 * 4);
+    const size_t lds = (size_t)MAXS * 8 + (size_t)nwords * 6;
+    if (lds > 64 * 1024 && !big_lds_allowed()) return ALBIREO_E_LAUNCH;
+    hipLaunchKernelGGL(k_state_init_bitmap, dim3((unsigned)B), dim3(INIT_NT), lds, stream, *state, V, nwords,
+                       prompt_offsets, prompt_ids, prompt_len, out_offsets, out_ids, out_len);
+    return hipGetLastError() == hipSuccess ? ALBIREO_OK : ALBIREO_E_LAUNCH;
+  }
   hipLaunchKernelGGL(k_state_init, dim3((unsigned)B), dim3(INIT_NT), 0, stream, *state, V, prompt_offsets, prompt_ids,
                      prompt_len, out_offsets, out_ids, out_len);
   return hipGetLastError() == hipSuccess ? ALBIREO_OK : ALBIREO_E_LAUNCH;
