@@ -756,6 +756,226 @@ __device__ void write_top_n(const OutArgs& a, Smem& s, const RowCtx& X, int64_t 
   __syncthreads();
 }
 
+constexpr double WFIX40 = 1099511627776.0;  // 2^40
+
+// ----------------------------------------------------------------------------------------------
+// Selections by digits: every thread holds up to EPT entries (a 32-bit key and a weight) in registers;
+// the key of the group where the cumulative weight, taken in key order, first reaches the target.  The
+// keys' common leading bits are skipped, the rest is resolved SD_DIG bits at a time through a histogram
+// of weights in LDS, a scan over it and the digit where the cumulative crosses.  Weights and sums are
+// integers, so the result does not depend on the order of the entries.
+// Bound: about six barriers a round (1.6 us); 128 to 2048 list entries take two or three rounds where the
+// two bitonic sorts they replace took 66 barrier-separated stages each.
+// ----------------------------------------------------------------------------------------------
+constexpr int SD_DIG = 11;
+constexpr int SD_B = 1 << SD_DIG;
+constexpr int SD_BPT = SD_B / NT;  // digits per thread in the scan
+static_assert(sizeof(Smem::scode) >= SD_B * sizeof(uint64_t) && SD_B % NT == 0, "digit histogram does not fit");
+
+// exclusive prefix of v over the threads in thread order; *total = sum over all threads
+__device__ __forceinline__ uint64_t block_excl_scan_u64(uint64_t v, Smem& s, uint64_t* total) {
+  uint64_t incl = v;
+  incl += dpp_mov64<DPP_ROW_SHR + 1>(incl);
+  incl += dpp_mov64<DPP_ROW_SHR + 2>(incl);
+  incl += dpp_mov64<DPP_ROW_SHR + 4>(incl);
+  incl += dpp_mov64<DPP_ROW_SHR + 8>(incl);
+  incl += dpp_mov64<DPP_ROW_BCAST15, 0xa>(incl);
+  incl += dpp_mov64<DPP_ROW_BCAST31, 0xc>(incl);
+  __syncthreads();
+  if (lane_id() == 63) s.red_q[wave_id()] = incl;
+  __syncthreads();
+  uint64_t off = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const uint64_t tw = s.red_q[w];
+    off += w < wave_id() ? tw : 0ull;
+    tot += tw;
+  }
+  *total = tot;
+  return off + incl - v;
+}
+
+// In the histogram h[0, SD_B), in descending (DESC) or ascending order: the bucket at which the
+// cumulative, continued from `before`, crosses the target -- reaches it (STRICT false) or exceeds it --
+// or -1 when it never does; `before` becomes the cumulative ahead of that bucket.  FRAC: the target
+// comes as a fraction of the histogram's total and leaves as that weight.
+template <bool DESC, bool STRICT, bool FRAC = false>
+__device__ __forceinline__ int digit_cross(Smem& s, const uint64_t* h, double& target, uint64_t& before) {
+  const int b0 = (int)threadIdx.x * SD_BPT;
+  uint64_t hv[SD_BPT], mine = 0;
+#pragma unroll
+  for (int q = 0; q < SD_BPT; ++q) {
+    hv[q] = h[DESC ? SD_B - 1 - (b0 + q) : b0 + q];
+    mine += hv[q];
+  }
+  if (threadIdx.x == 0) s.bc_i[0] = -1;  // ordered before the writes below by the scan's barriers
+  uint64_t tot;
+  uint64_t cum = before + block_excl_scan_u64(mine, s, &tot);
+  if (FRAC) target *= (double)tot;
+  auto reached = [&](uint64_t c) { return STRICT ? (double)c > target : (double)c >= target; };
+  if (!reached(cum) && reached(cum + mine)) {  // at most one thread
+    int q = 0;
+#pragma unroll
+    for (int i = 0; i < SD_BPT - 1; ++i)
+      if (q == i && !reached(cum + hv[i])) {
+        cum += hv[i];
+        q = i + 1;
+      }
+    s.bc_i[0] = DESC ? SD_B - 1 - (b0 + q) : b0 + q;
+    s.bc_q[0] = cum;
+  }
+  __syncthreads();
+  const int b = s.bc_i[0];
+  if (b >= 0) before = s.bc_q[0];
+  __syncthreads();
+  return b;
+}
+
+// The key of the crossing group among the entries with w != 0, or false when the target is not reached.
+// wt[q] == 0 marks an absent entry.
+template <bool DESC, bool STRICT>
+__device__ __forceinline__ bool digit_select(Smem& s, const uint32_t (&key)[EPT], const uint64_t (&wt)[EPT],
+                                             double target, uint64_t before, uint32_t& out_key) {
+  uint64_t* h = reinterpret_cast<uint64_t*>(s.scode);
+  uint32_t kmin = ~0u, kor = 0;
+#pragma unroll
+  for (int q = 0; q < EPT; ++q)
+    if (wt[q]) kmin = min(kmin, key[q]);
+  kmin = wave_min_u32(kmin);
+  __syncthreads();
+  if (lane_id() == 0) s.red_u[wave_id()] = kmin;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) kmin = min(kmin, s.red_u[w]);
+  if (kmin == ~0u) return false;  // no entry (a key of all ones would be a NaN)
+#pragma unroll
+  for (int q = 0; q < EPT; ++q)
+    if (wt[q]) kor |= key[q] ^ kmin;  // the bits in which any key differs from the smallest
+  kor = wave_or(kor);
+  __syncthreads();
+  if (lane_id() == 0) s.red_u[wave_id()] = kor;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) kor |= s.red_u[w];
+  int bits = 32 - __clz((int)kor);  // keys agree above bit `bits`
+  uint32_t prefix = bits < 32 ? (kmin >> bits) << bits : 0u;
+  do {
+    const int shift = max(bits - SD_DIG, 0);
+    const uint32_t hi = bits < 32 ? ~0u << bits : 0u;
+    const uint32_t dm = (1u << (bits - shift)) - 1u;
+    for (int b = threadIdx.x; b < SD_B; b += NT) h[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < EPT; ++q)
+      if (wt[q] && (key[q] & hi) == prefix)
+        atomicAdd((unsigned long long*)&h[(key[q] >> shift) & dm], (unsigned long long)wt[q]);
+    __syncthreads();
+    const int d = digit_cross<DESC, STRICT>(s, h, target, before);
+    if (d < 0) return false;
+    prefix |= (uint32_t)d << shift;
+    bits = shift;
+  } while (bits > 0);
+  out_key = prefix;
+  return true;
+}
+
+// The n_top largest of the candidates t[0, nt) (LDS), ranked by counting, to the row's outputs.
+__device__ __forceinline__ void write_top_ranked(const OutArgs& a, const RowCtx& X, int64_t row, const uint64_t* t,
+                                                 int nt) {
+  for (int i = threadIdx.x; i < max(nt, a.n_top); i += NT) {
+    if (i < nt) {
+      const uint64_t k = t[i];
+      int rk = 0;
+#pragma unroll 8
+      for (int j = 0; j < nt; ++j) rk += t[j] > k ? 1 : 0;
+      if (rk < a.n_top) {
+        a.out_top_ids[row * a.n_top + rk] = cand_pos(k);
+        a.out_top_logprobs[row * a.n_top + rk] = (float)((double)cand_z(k) - (double)X.m - X.L);
+      }
+    } else if (i < a.n_top) {
+      a.out_top_ids[row * a.n_top + i] = -1;
+      a.out_top_logprobs[row * a.n_top + i] = -INFINITY;
+    }
+  }
+}
+
+// The n_top largest of s.sk[0, n) with z >= row_beta (which holds them all: row_beta is at most the
+// row's n_top-th largest value), ranked by counting, to the row's outputs.
+__device__ __forceinline__ void write_top_small(const OutArgs& a, Smem& s, const RowCtx& X, int64_t row, int n) {
+  uint64_t* t = reinterpret_cast<uint64_t*>(s.l_z);  // the list arrays: 24 KB
+  constexpr int TCAP = 3 * LCAP / 2;
+  __syncthreads();
+  if (threadIdx.x == 0) s.bc_i[2] = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const uint64_t k = s.sk[i];
+    if (cand_z(k) >= X.row_beta) t[min(atomicAdd(&s.bc_i[2], 1), TCAP - 1)] = k;
+  }
+  __syncthreads();
+  write_top_ranked(a, X, row, t, s.bc_i[2]);  // at most LCAP <= TCAP
+  __syncthreads();
+}
+static_assert(3 * LCAP * 4 / 8 >= LCAP, "top-n staging below the candidate list");
+
+// A sampled row whose candidate list holds more than SMALL_LIST entries: top-k, min-p, top-p and the
+// draw by digit selections over the list (masses exp(z - m) in units of 2^-40).
+__device__ __noinline__ Resolution resolve_mid(const OutArgs a, Smem& s, const RowState R, const RowCtx X,
+                                               Resolution res) {
+  const int n = X.n_list;
+  const float m = X.m;
+  uint32_t key[EPT], pos[EPT];
+  uint64_t w[EPT], wt[EPT];
+#pragma unroll
+  for (int q = 0; q < EPT; ++q) {
+    const int i = (int)threadIdx.x + q * NT;
+    const uint64_t k = i < n ? s.sk[i] : 0ull;
+    key[q] = (uint32_t)(k >> 32);
+    pos[q] = (uint32_t)cand_pos(k);
+    w[q] = i < n ? (uint64_t)((double)__expf(cand_z(k) - m) * WFIX40) : 0ull;
+  }
+  float tau2 = X.tau_m;
+  uint32_t kk;
+  if (R.k_on && R.k <= n) {
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) wt[q] = (int)threadIdx.x + q * NT < n ? 1ull : 0ull;
+    if (digit_select<true, false>(s, key, wt, (double)R.k, 0, kk)) tau2 = fmaxf(tau2, key2f(kk));
+  }
+  float tau = tau2;
+  if (R.topp_on) {
+    uint64_t z2 = 0;
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+      wt[q] = key2f(key[q]) >= tau2 ? w[q] : 0ull;
+      z2 += wt[q];
+    }
+    const double Z2 = (R.k_on || R.minp_on) ? (double)block_sum_u64(z2, s) : (double)X.zfull * WFIX40;
+    // the top group always enters: a target of at least one unit
+    if (digit_select<true, false>(s, key, wt, fmax((double)R.p * Z2, 1.0), 0, kk)) tau = fmaxf(tau2, key2f(kk));
+  }
+  uint64_t zs = 0;
+#pragma unroll
+  for (int q = 0; q < EPT; ++q) {
+    wt[q] = key2f(key[q]) >= tau ? w[q] : 0ull;
+    zs += wt[q];
+  }
+  zs = block_sum_u64(zs, s);
+  // the first position, in ascending order, whose cumulative exceeds u Z (the last of positive mass when
+  // rounding leaves none)
+  const double target = fmax(fmin((double)R.u * (double)zs, (double)zs - 1.0), 0.0);
+  if (digit_select<false, true>(s, pos, wt, target, 0, kk)) {
+    res.id = (int)kk;
+#pragma unroll
+    for (int q = 0; q < EPT; ++q)
+      if (wt[q] && pos[q] == kk) s.bc_f[0] = key2f(key[q]);
+    __syncthreads();
+    res.zid = s.bc_f[0];
+  }
+  res.id_here = 1;
+  if (a.n_top > 0) write_top_small(a, s, X, R.row, n);
+  __syncthreads();
+  return res;
+}
+
 // ----------------------------------------------------------------------------------------------
 // Radix selection over the chunk (re-read from memory) and the extras (general path).
 // Finds the largest key K such that the weight of eligible elements (finite z >= zlo) with
@@ -844,11 +1064,8 @@ __device__ bool radix_select(Smem& s, const RowState& R, const RowCtx& X, float 
 // only larger values and equal values share a bucket.  The bucket where the cumulative crosses is
 // staged in LDS and finished by the byte radix there, from the cumulative of the buckets above it; a
 // bucket too large to stage (or a target of 0) goes to radix_select.
-constexpr int SD_B = 2048;
 constexpr float SD_SCALE = 64.0f;
 constexpr int SD_CAP = 2 * LCAP;  // 32-bit keys in the 64-bit candidate list area
-static_assert(sizeof(Smem::scode) >= SD_B * sizeof(uint64_t) && SD_B % NT == 0, "distance histogram does not fit");
-
 __device__ __forceinline__ int dist_bucket(float z, float m) {
   const float d = __fmul_rn(__fsub_rn(m, z), SD_SCALE);
   return d < (float)(SD_B - 1) ? (int)d : SD_B - 1;
@@ -988,7 +1205,6 @@ __device__ bool select_dist(Smem& s, const RowState& R, const RowCtx& X, float z
 // ----------------------------------------------------------------------------------------------
 constexpr int SMALL_LIST = 128;
 constexpr float WFIX = 16777216.0f;        // 2^24
-constexpr double WFIX40 = 1099511627776.0;  // 2^40 (kept mass reported as a float)
 __device__ __forceinline__ uint32_t wfix(float w) { return (uint32_t)__builtin_fmaf(w, WFIX, 0.5f); }
 
 // LDS totals of the counting resolver, in the general path's histogram (unused by this path)
@@ -1581,6 +1797,421 @@ __device__ __noinline__ Resolution resolve_general(const OutArgs a, Smem& s, con
     if (leader) write_top_n(a, s, X, R.row, min(nl, LCAP));
   }
   __syncthreads();
+  return res;
+}
+
+// ----------------------------------------------------------------------------------------------
+// A sampled single-chunk row with no small kept set and no top-k: the nucleus cut and the draw.
+//
+// The weight of a value is w = 2^(z L2E - gref) with gref just above m L2E, so that every w is below 1
+// (the common factor cancels).  Nucleus rows first take a histogram of fixed-point weights (units of
+// 2^-32) over the distance from the row maximum, 64 buckets per unit: fl(64 m - 64 z) is monotone in z,
+// so a lower bucket holds only larger values and equal values share a bucket.  The second pass stages
+// the bucket where the cumulative crosses p times the total (finished by digit_select) and sums the
+// weights of the buckets above it per group of GSL slots of every thread, a group being GSL * NT * VEC
+// consecutive positions; rows without top-p take this pass alone, over z >= the min-p cut.  The draw
+// then picks the group, takes its weights again per slot, scans them in position order and walks the
+// crossing slot's elements.  Sums over registers are taken in a fixed order (eight weights in fp32, the
+// rest in double); LDS sums of single values are integers.
+//
+// Bound: VALU on the row's one CU, about 15 instructions per value and pass at 4 cycles per wave
+// instruction (an exponential four times that).  The passes are free of branches, so that the eight
+// values of a slot overlap: with the LDS add under a test per value, a 128256-logit row spent 57-87 us
+// in the histogram.  The row is read again (256 KB, from the caches) rather than kept in the caller's
+// registers, which cost every other row of the kernel 2-4 % in spilled scalars.  64 rows of 128256 bf16
+// logits: nucleus rows 230-257 us with selections and a draw over six and more passes through memory and
+// double conversions, 64-75 us here; plain rows 105 -> 38 us.
+// ----------------------------------------------------------------------------------------------
+constexpr int GSL = 4;                              // slots of a thread per group
+constexpr int NGRP = (JMAX + GSL - 1) / GSL;        // groups of a row
+constexpr double FIX44 = 17592186044416.0;          // 2^44
+static_assert(GSL * NT <= SD_B, "a group's slots exceed the scan array");
+static_assert(sizeof(Smem::scode) >= 2 * SD_B * sizeof(uint64_t), "group scan arrays do not fit");
+
+struct OpenLds {  // in the list arrays (l_z, l_w, l_p), free on this path
+  double gs[NGRP][NW];       // per group and wave: the kept weight of the row's slots
+  uint64_t gx[NGRP + 2];     // head, groups, tail: the extras' and the staged bucket's kept weight
+  int32_t n_top;             // top-n candidates staged (at most OPEN_TOP fit)
+};
+constexpr int OPEN_TOP = 1024;  // top-n candidates staged behind OpenLds
+
+constexpr int OPEN_TOP_OFF = 4096;  // bytes into the list arrays
+static_assert(sizeof(OpenLds) <= OPEN_TOP_OFF && OPEN_TOP_OFF + OPEN_TOP * 8 <= 3 * LCAP * 4,
+              "general-path sums and top-n candidates do not fit");
+
+__device__ __forceinline__ double dpp_add_f64(double v, uint64_t w) { return v + __longlong_as_double((long long)w); }
+__device__ __forceinline__ double wave_incl_scan_f64(double v) {
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_SHR + 1>((uint64_t)__double_as_longlong(v)));
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_SHR + 2>((uint64_t)__double_as_longlong(v)));
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_SHR + 4>((uint64_t)__double_as_longlong(v)));
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_SHR + 8>((uint64_t)__double_as_longlong(v)));
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_BCAST15, 0xa>((uint64_t)__double_as_longlong(v)));
+  v = dpp_add_f64(v, dpp_mov64<DPP_ROW_BCAST31, 0xc>((uint64_t)__double_as_longlong(v)));
+  return v;
+}
+__device__ __forceinline__ double lane_f64(double v, int i) {
+  return __longlong_as_double((long long)lane_u64((uint64_t)__double_as_longlong(v), i));
+}
+// sum of a slot's VEC weights, in a fixed order
+template <int VEC>
+__device__ __forceinline__ float slot_sum(const float (&w)[VEC]) {
+  float a = (w[0] + w[1]) + (w[2] + w[3]);
+  if constexpr (VEC == 8) a += (w[4] + w[5]) + (w[6] + w[7]);
+  return a;
+}
+
+// f(g, d) for the row's groups in order: d[q] = slot (g GSL + q) NT + thread, penalised elements (extras)
+// and slots past the row -inf; the next group's loads are in flight meanwhile (two register sets in
+// turn: a copy between them would wait for the loads).  The loads name the global address space: a
+// pointer that went through the stack would otherwise load as a generic one and wait for LDS too.
+template <class DT, class F>
+__device__ __forceinline__ void for_groups(const RowState& R, const Smem& s, int g0, int g1, F&& f) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int ns = (int)(R.s1 - R.s0);
+  if (ns <= 0 || g0 >= g1) return;
+  uint4 da[GSL], db[GSL];
+  auto load = [&](uint4 (&x)[GSL], int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < GSL; ++q) {
+      const int64_t slot = R.s0 + min((g * GSL + q) * NT + (int)threadIdx.x, ns - 1);
+      const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)(R.rowp + slot_off<DT>(R, slot));
+      x[q] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+  };
+  auto use = [&](const uint4 (&x)[GSL], int g) __attribute__((always_inline)) {
+    uint4 d[GSL];
+#pragma unroll
+    for (int q = 0; q < GSL; ++q) {
+      const int l = (g * GSL + q) * NT + (int)threadIdx.x;
+      d[q] = x[q];
+      if (R.pen_on) d[q] = mask_slot<DT>(R, s, R.s0 + min(l, ns - 1), d[q]);
+      const bool dead = l >= ns;
+      d[q].x = dead ? DT::NEG : d[q].x;
+      d[q].y = dead ? DT::NEG : d[q].y;
+      d[q].z = dead ? DT::NEG : d[q].z;
+      d[q].w = dead ? DT::NEG : d[q].w;
+    }
+    f(g, d);
+  };
+  load(da, g0);
+#pragma unroll 1
+  for (int g = g0; g < g1; g += 2) {
+    load(db, min(g + 1, g1 - 1));
+    use(da, g);
+    if (g + 1 >= g1) break;
+    load(da, min(g + 2, g1 - 1));
+    use(db, g + 1);
+  }
+}
+
+// Returns res with id_here = -1, nothing decided, when the crossing bucket or the top-n candidates do not
+// fit the staging, or when m is so large that the rounding of m L2E would show in the weights' scale.
+constexpr float OPEN_MAX_M = 16384.0f;
+template <class DT>
+__device__ __noinline__ Resolution resolve_open(const OutArgs a, Smem& s, const RowState R, const RowCtx X,
+                                                Resolution res) {
+  constexpr int VEC = DT::VEC;
+  const int t = threadIdx.x;
+  const float r = R.r, m = X.m;
+  const int n_ext = X.n_ext;
+  const float gref = __fmul_rn(m, L2E) + fmaxf(fabsf(m) * 1e-6f, 1e-6f);
+  OpenLds& G = *reinterpret_cast<OpenLds*>(s.l_z);
+  uint64_t* h = reinterpret_cast<uint64_t*>(s.scode);
+  const int fail = -1;
+  if (!(fabsf(m) <= OPEN_MAX_M)) {
+    res.id_here = fail;
+    return res;
+  }
+  auto weight = [&](float z) __attribute__((always_inline)) -> float {
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(z, L2E, -gref));
+  };
+  auto fix32 = [&](float w) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(w * 4294967296.0f); };
+  const float m64 = m * SD_SCALE;  // exact
+  auto dist = [&](float z) __attribute__((always_inline)) -> float { return __builtin_fmaf(z, -SD_SCALE, m64); };
+  auto group_of = [&](int pos) __attribute__((always_inline)) -> int {  // 0: head, 1 .. NGRP, NGRP + 1: tail
+    if (pos < R.head) return 0;
+    if (pos >= R.tail_lo) return NGRP + 1;
+    return ((pos - R.head) / VEC) / (GSL * NT) + 1;
+  };
+  const int ngr = ((int)(R.s1 - R.s0) + GSL * NT - 1) / (GSL * NT);  // groups of this row
+  const bool nucleus = R.topp_on && R.p > 0.0f;
+  float tau = (R.topp_on && !nucleus) ? m : X.tau_m;  // p <= 0: the top group only
+  float f_lt = 0.0f, f_le = 0.0f;                     // nucleus: dist below f_lt is kept, below f_le staged
+  uint64_t before = 0;
+  double target = (double)R.p;
+
+  // ---- the distance histogram and its crossing bucket ----
+  if (nucleus) {
+    __syncthreads();
+    for (int b = t; b < SD_B; b += NT) h[b] = 0;
+    __syncthreads();
+    auto add = [&](float z) __attribute__((always_inline)) {  // no branch: a value below the cut adds 0
+      const uint32_t u = z >= tau ? fix32(weight(z)) : 0u;
+      const int b = (int)fminf(dist(z), (float)(SD_B - 1));
+      atomicAdd((unsigned long long*)&h[b], (unsigned long long)u);
+    };
+    for_groups<DT>(R, s, 0, ngr, [&](int, const uint4 (&d)[GSL]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < GSL; ++q)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) add(DT::get(d[q], e) * r);
+    });
+    FOR_EXTRAS(s, n_ext, {
+      (void)pos;
+      add(canon(x, r));
+    })
+    __syncthreads();
+    const int bb = digit_cross<false, false, true>(s, h, target, before);
+    if (bb < 0) {
+      res.id_here = fail;
+      return res;
+    }
+    f_lt = (float)bb;
+    f_le = bb == SD_B - 1 ? INFINITY : (float)(bb + 1);
+  }
+
+  // ---- kept weight per group; the crossing bucket's values staged ----
+  __syncthreads();
+  if (t < NGRP + 2) G.gx[t] = 0;
+  if (t < NGRP * NW) G.gs[t / NW][t % NW] = 0.0;
+  if (t == 0) {
+    s.n_list = 0;
+    G.n_top = 0;
+  }
+  __syncthreads();
+  // the row's top n: its values at or above row_beta, at most the row's n_top-th largest
+  uint64_t* topk = reinterpret_cast<uint64_t*>(reinterpret_cast<unsigned char*>(s.l_z) + OPEN_TOP_OFF);
+  const float beta = X.row_beta;
+  auto stage_top = [&](float z, int pos) __attribute__((always_inline)) {
+    if (z > -INFINITY && z >= beta) {
+      const int i = atomicAdd(&G.n_top, 1);
+      if (i < OPEN_TOP) topk[i] = cand_key(z, pos);
+    }
+  };
+  auto stage = [&](float z, int pos) __attribute__((always_inline)) {
+    if (z > -INFINITY && z >= tau) {
+      const int i = atomicAdd(&s.n_list, 1);
+      if (i < LCAP) s.sk[i] = ((uint64_t)f2key(z) << 32) | (uint32_t)pos;
+    }
+  };
+  auto pass = [&](auto NUC, auto TOP) __attribute__((always_inline)) {
+    constexpr bool nuc = decltype(NUC)::value, top = decltype(TOP)::value;
+    for_groups<DT>(R, s, 0, ngr, [&](int g, const uint4 (&d)[GSL]) __attribute__((always_inline)) {
+      double acc = 0.0;
+      // bit q VEC + e: element e of slot q is in the crossing bucket, is a top-n candidate
+      uint32_t eq = 0, tp = 0;
+#pragma unroll
+      for (int q = 0; q < GSL; ++q) {
+        float w[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float z = DT::get(d[q], e) * r;
+          const float wz = weight(z);
+          if constexpr (top) tp |= (z >= beta ? 1u : 0u) << (q * VEC + e);
+          if constexpr (nuc) {
+            const float f = dist(z);
+            w[e] = f < f_lt ? wz : 0.0f;
+            eq |= ((f < f_le ? 1u : 0u) & (f < f_lt ? 0u : 1u)) << (q * VEC + e);
+          } else {
+            w[e] = z >= tau ? wz : 0.0f;
+          }
+        }
+        acc += (double)slot_sum<VEC>(w);
+      }
+      auto each = [&](uint32_t bits, auto&& f) __attribute__((always_inline)) {  // f(z, position)
+        while (bits) {
+          const int i = __builtin_ctz(bits), q = i / VEC, e = i % VEC;
+          bits &= bits - 1u;
+          uint4 dd = d[0];
+#pragma unroll
+          for (int k = 1; k < GSL; ++k) {
+            dd.x = q == k ? d[k].x : dd.x;
+            dd.y = q == k ? d[k].y : dd.y;
+            dd.z = q == k ? d[k].z : dd.z;
+            dd.w = q == k ? d[k].w : dd.w;
+          }
+          f(canon(DT::get(dd, e), r), R.head + (int)(R.s0 + (g * GSL + q) * NT + t) * VEC + e);
+        }
+      };
+      if constexpr (nuc) each(eq, stage);
+      if constexpr (top) each(tp, stage_top);
+      acc = wave_incl_scan_f64(acc);
+      if (lane_id() == 63) G.gs[g][wave_id()] = acc;
+    });
+    FOR_EXTRAS(s, n_ext, {
+      const float z = canon(x, r);
+      if constexpr (top) stage_top(z, pos);
+      bool in;
+      if constexpr (nuc) {
+        const float f = dist(z);
+        in = f < f_lt;
+        if (f < f_le && !in) stage(z, pos);
+      } else {
+        in = z >= tau;
+      }
+      if (in) atomicAdd((unsigned long long*)&G.gx[group_of(pos)], (unsigned long long)((double)weight(z) * FIX44));
+    })
+  };
+  if (a.n_top > 0) {
+    if (nucleus) pass(std::true_type{}, std::true_type{});
+    else pass(std::false_type{}, std::true_type{});
+  } else {
+    if (nucleus) pass(std::true_type{}, std::false_type{});
+    else pass(std::false_type{}, std::false_type{});
+  }
+  __syncthreads();
+  if (nucleus) {
+    const int n = s.n_list;
+    if (n > LCAP) {  // uniform
+      res.id_here = fail;
+      return res;
+    }
+    uint32_t key[EPT], kk;
+    uint64_t wt[EPT];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+      const int i = t + q * NT;
+      key[q] = i < n ? (uint32_t)(s.sk[i] >> 32) : 0u;
+      wt[q] = i < n ? (uint64_t)fix32(weight(key2f(key[q]))) : 0ull;
+    }
+    if (!digit_select<true, false>(s, key, wt, target, before, kk)) {
+      res.id_here = fail;
+      return res;
+    }
+    tau = fmaxf(tau, key2f(kk));
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+      const int i = t + q * NT;
+      const float z = key2f(key[q]);
+      if (i < n && z >= tau)
+        atomicAdd((unsigned long long*)&G.gx[group_of((int)(uint32_t)s.sk[i])],
+                  (unsigned long long)((double)weight(z) * FIX44));
+    }
+    __syncthreads();
+  }
+
+  // ---- the draw's group: lane g holds group g's weight, the same in every wave ----
+  double gsum = 0.0;
+  {
+    const int l = lane_id();
+    if (l < NGRP + 2) {
+      gsum = (double)G.gx[l] / FIX44;
+      if (l >= 1 && l <= NGRP) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) gsum += G.gs[l - 1][w];
+      }
+    }
+  }
+  const double gincl = wave_incl_scan_f64(gsum);
+  const double zs = lane_f64(gincl, 63);
+  const double tgt = fmax((double)R.u * zs, 0.0);
+  const uint64_t over = __ballot(gincl > tgt && gsum > 0.0), some = __ballot(gsum > 0.0);
+  // rounding that leaves no cumulative above the target: the last element of positive weight of the
+  // group, the slot and so on, by an infinite target from there on
+  const int gi = over ? (int)__builtin_ctzll(over) : 63 - (int)__builtin_clzll(some | 1ull);
+  double cum0 = lane_f64(gincl - gsum, gi);
+  double ftgt = over ? tgt : INFINITY;
+
+  // ---- inside the group: the weights of its slots in position order ----
+  int p_lo, p_hi;  // the positions left to walk (at most VEC of them)
+  if (gi >= 1 && gi <= NGRP) {
+    double* fm = reinterpret_cast<double*>(s.scode);
+    uint64_t* fx = reinterpret_cast<uint64_t*>(s.scode) + SD_B;
+    for (int i = t; i < GSL * NT; i += NT) {
+      fm[i] = 0.0;
+      fx[i] = 0;
+    }
+    for_groups<DT>(R, s, gi - 1, min(gi, ngr), [&](int, const uint4 (&d)[GSL]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < GSL; ++q) {
+        float w[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float z = DT::get(d[q], e) * r;
+          w[e] = z >= tau ? weight(z) : 0.0f;
+        }
+        fm[q * NT + t] = (double)slot_sum<VEC>(w);
+      }
+    });
+    __syncthreads();
+    const int b0 = R.head + (gi - 1) * GSL * NT * VEC;  // the group's first position
+    FOR_EXTRAS(s, n_ext, {
+      const float z = canon(x, r);
+      if (z >= tau && group_of(pos) == gi)
+        atomicAdd((unsigned long long*)&fx[(pos - b0) / VEC], (unsigned long long)((double)weight(z) * FIX44));
+    })
+    if (t == 0) {
+      s.bc_i[0] = INT32_MAX;
+      s.bc_i[1] = -1;
+    }
+    __syncthreads();
+    double v[GSL], mine = 0.0;
+#pragma unroll
+    for (int q = 0; q < GSL; ++q) {
+      v[q] = fm[t * GSL + q] + (double)fx[t * GSL + q] / FIX44;
+      mine += v[q];
+    }
+    const double incl = wave_incl_scan_f64(mine);
+    if (lane_id() == 63) s.red_q[wave_id()] = (uint64_t)__double_as_longlong(incl);
+    __syncthreads();
+    double cum = cum0;
+    for (int w = 0; w < wave_id(); ++w) cum += __longlong_as_double((long long)s.red_q[w]);
+    cum += incl - mine;
+    int first = INT32_MAX, last = -1;
+    double before_first = 0.0, before_last = 0.0;
+#pragma unroll
+    for (int q = 0; q < GSL; ++q) {
+      if (v[q] > 0.0) {
+        if (first == INT32_MAX && cum + v[q] > ftgt) {
+          first = t * GSL + q;
+          before_first = cum;
+        }
+        last = t * GSL + q;
+        before_last = cum;
+      }
+      cum += v[q];
+    }
+    if (first != INT32_MAX) atomicMin(&s.bc_i[0], first);
+    if (last >= 0) atomicMax(&s.bc_i[1], last);
+    __syncthreads();
+    const bool crossed = s.bc_i[0] != INT32_MAX;
+    const int ent = crossed ? s.bc_i[0] : s.bc_i[1];
+    if (ent >= 0 && (crossed ? first == ent : last == ent))
+      s.bc_q[0] = (uint64_t)__double_as_longlong(crossed ? before_first : before_last);
+    if (!crossed) ftgt = INFINITY;
+    __syncthreads();
+    cum0 = __longlong_as_double((long long)s.bc_q[0]);
+    p_lo = b0 + max(ent, 0) * VEC;
+    p_hi = min(p_lo + VEC, R.tail_lo);
+  } else {
+    p_lo = gi == 0 ? 0 : R.tail_lo;
+    p_hi = gi == 0 ? R.head : R.V;
+  }
+
+  // ---- the slot's elements in position order ----
+  {
+    const int l = lane_id();
+    const int pos = p_lo + l;
+    const bool in = l < VEC && pos < p_hi;
+    const float z = in ? canon(x_at<DT>(s, R, n_ext, pos), r) : -INFINITY;
+    const double w = (in && z >= tau) ? (double)weight(z) : 0.0;
+    const double cum = cum0 + wave_incl_scan_f64(w);
+    const uint64_t hit = __ballot(w > 0.0 && cum > ftgt), any = __ballot(w > 0.0);
+    const int e = hit ? (int)__builtin_ctzll(hit) : 63 - (int)__builtin_clzll(any | 1ull);
+    res.id = p_lo + e;
+    res.zid = lane_f32(z, e);
+    res.id_here = 1;
+  }
+  res.tau = tau;
+
+  if (a.n_top > 0) {
+    const int n = G.n_top;  // uniform
+    if (n > OPEN_TOP) {
+      res.id_here = fail;
+      return res;
+    }
+    write_top_ranked(a, X, R.row, topk, n);
+  }
   return res;
 }
 
@@ -2341,7 +2972,16 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
     }
     float beta_list = beta_S;
     if (a.mode == 0 && a.n_top > 0) beta_list = fminf(beta_list, row_beta);
-    const bool no_bound = !(beta_list > -INFINITY);
+    // A bound at or below every thread maximum of two waves is left to the general path with nothing
+    // gathered.  Where the row's values are spread alike over the threads, n candidates give a wave
+    // that property with probability (1 - e^(-n / 512))^64, so two of eight have it in 6 % of the rows of
+    // 1600 candidates, 75 % at LCAP = 2048 and 96 % at 2300; a list that overflows after all costs its
+    // 14 us of gathering for nothing.
+    int w_all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) w_all += beta_list <= s.wp[4][w] ? 1 : 0;
+    const bool loose = !MULTI && a.mode == 0 && !R.greedy && !R.k_on && w_all >= 2;
+    const bool no_bound = loose || !(beta_list > -INFINITY);
 
     // ---------------- gather candidates z >= beta_list into the LDS list ----------------
     // (the list counter was cleared at the start of the row)
@@ -2351,7 +2991,10 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
       // a candidate is an element whose product x r is >= bl (canon only turns -0 into +0)
       const int pos_t = R.head + (int)(R.s0 + threadIdx.x) * DT::VEC;
       // the best pair, from its register copy: one list claim per wave, each lane's place being its
-      // exclusive prefix of the candidate counts
+      // exclusive prefix of the candidate counts.  A claim past the list's end leaves the count above
+      // its capacity, which is all the resolution needs: the wave gathers no further (rows whose bound
+      // lets most of the row through took 30 us here).
+      bool full = false;
       {
         uint32_t cm = 0;  // bit e: element e of the pair (slot 2 bj, then 2 bj + 1)
 #pragma unroll
@@ -2365,9 +3008,11 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
         if (total > 0) {
           int base = 0;
           if (lane_id() == 0) base = atomicAdd(&s.n_list, total);
-          int idx = __builtin_amdgcn_readfirstlane(base) + incl - c;
+          base = __builtin_amdgcn_readfirstlane(base);
+          full = base + total > LCAP;
+          int idx = base + incl - c;
           const int pb = pos_t + 2 * bj * NT * DT::VEC;
-          while (cm) {
+          while (cm && !full) {
             const int b = __ffs(cm) - 1;
             cm &= cm - 1;
             const int e = b % DT::VEC;
@@ -2382,7 +3027,7 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
       // truncating a monotone key keeps smax >= bl => code(smax) >= code(bl)), pass 2 from the
       // registers
       const bool more = b2 >= bl;
-      if (__ballot(more)) {
+      if (!full && __ballot(more)) {
         const uint32_t tcode = f2key(bl) >> 16;
         // an opaque copy of the thread index, so that the code addresses are not shared with the
         // online pass's stores (which would keep them live, spilled, across the pass)
@@ -2417,7 +3062,9 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
           if (total > 0) {
             int base = 0;
             if (lane_id() == 0) base = atomicAdd(&s.n_list, total);
-            int idx = __builtin_amdgcn_readfirstlane(base) + incl - c;
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (base + total > LCAP) break;
+            int idx = base + incl - c;
             const int pp = pos_t + 2 * i * NT * DT::VEC;
             while (cm) {
               const int b = __ffs(cm) - 1;
@@ -2441,13 +3088,16 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
     __syncthreads();  // D
     if (fx_late) fold_extras(row_mref, row_s);  // P == 1 here: the row's own sums
     // the full-vocabulary normaliser in double, now that the row's registers are released
-    {
+    int n_list = s.n_list;
+    bool overflow = !skip && (no_bound || n_list > LCAP || n_list == 0);
+    // where only the logprob needs it and wave 0 alone finishes the row, wave 1 evaluates it meanwhile
+    const bool late_L = !MULTI && a.mode == 0 && a.n_top == 0 && !skip && !overflow && n_list <= SMALL_LIST &&
+                        (R.greedy || R.k_on || R.minp_on || !R.topp_on);
+    if (!late_L) {
       const RowDoubles RD = row_doubles(row_mref, row_s, m);
       X.L = RD.L;
       X.zfull = RD.zfull;
     }
-    int n_list = s.n_list;
-    bool overflow = !skip && (no_bound || n_list > LCAP || n_list == 0);
     if (P > 1) n_list = union_lists(s, R, X, n_list, overflow);
     X.n_list = n_list;
 
@@ -2467,12 +3117,31 @@ __device__ __forceinline__ void process_row(const KArgs& a, Smem& s, RowCtx& X, 
       if (leader) {
         if (X.n_list <= SMALL_LIST) {
           res = resolve_count(oa, s, R, X, res);  // every thread holds the result
+          if (late_L) {
+            if (wave_id() == 1) {
+              const RowDoubles RD = row_doubles(row_mref, row_s, m);
+              if (lane_id() == 0) s.bc_q[0] = (uint64_t)__double_as_longlong(RD.L);
+            }
+            __syncthreads();
+            X.L = __longlong_as_double((long long)s.bc_q[0]);
+          }
+        } else if (a.mode == 0 && !R.greedy) {
+          res = resolve_mid(oa, s, R, X, res);
         } else {
           res = resolve_list(oa, s, R, X, res);
         }
       }
     } else {
-      res = resolve_general<DT>(oa, s, R, X, res);
+      bool open = false;  // rows with no small kept set and no top-k
+      if constexpr (!MULTI) {
+        open = a.mode == 0 && !R.greedy && !R.k_on;
+        if (open) {
+          const Resolution ro = resolve_open<DT>(oa, s, R, X, res);
+          open = ro.id_here >= 0;
+          if (open) res = ro;
+        }
+      }
+      if (!open) res = resolve_general<DT>(oa, s, R, X, res);
     }
 
     // ---------------- per-row outputs ----------------
