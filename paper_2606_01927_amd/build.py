@@ -10,7 +10,8 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", n) for n in ("albireo.hip", "stream.hip", "state.hip", "penalties.hip")]
+SRCS = [os.path.join(HERE, "csrc", n) for n in ("albireo.hip", "stream.hip", "state.hip", "penalties.hip",
+                                              "filter.hip")]
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libalbireo.so")
 
