@@ -489,11 +489,12 @@ __device__ __forceinline__ int pos_of_rank(const SSm& s, int nwords, int64_t e_b
 // unaligned head of chunk 0, the tail of the last chunk) have bits too.  Every history id in the
 // chunk's positions marks its bit; word prefix counts number the marked positions; per number, the
 // output count (bits 0-30) and the prompt mark (bit 31).  The first HPT * CT history ids come from the
-// caller's registers (hreg, this thread's share), the rest from memory.  Returns the number of tracked
+// caller's registers (hreg, this thread's share), the rest from memory.  EXT false: the call has neither prompt nor
+// state.  Returns the number of tracked
 // positions (at most XCAP; past that the highest positions are left out and FLAG_LIMIT is set) and ORs
 // FLAG_BAD_INPUT / FLAG_LIMIT into *fl.
 // ----------------------------------------------------------------------------------------------
-template <int HPT>
+template <int HPT, bool EXT = true>
 __device__ __forceinline__ int build_overlay(const SArgs& a, const SRow& R, SSm& s, int c, int64_t s0, int64_t s1,
                                              int vec, const int32_t (&hreg)[HPT > 0 ? HPT : 1], uint32_t* fl) {
   const int t = threadIdx.x;
@@ -547,9 +548,11 @@ __device__ __forceinline__ int build_overlay(const SArgs& a, const SRow& R, SSm&
     if (R.h_lo + t + (int64_t)q * CT < h_reg_end) mark(hreg[q]);
   });
   for_hist([&](int32_t id, int64_t) { mark(id); });
-  for_ids(a.prompt_ids, R.p_lo, R.p_hi, [&](int32_t id, int64_t) { mark(id); });
   const int32_t* st_row = a.st_ids + R.row * a.st_cap;
-  for_ids(st_row, 0, R.st_n, [&](int32_t id, int64_t) { mark(id); });
+  if constexpr (EXT) {
+    for_ids(a.prompt_ids, R.p_lo, R.p_hi, [&](int32_t id, int64_t) { mark(id); });
+    for_ids(st_row, 0, R.st_n, [&](int32_t id, int64_t) { mark(id); });
+  }
   if (bad) *fl |= FLAG_BAD_INPUT;
   __syncthreads();
   const int wpt = (nwords + CT - 1) / CT;
@@ -594,12 +597,25 @@ __device__ __forceinline__ int build_overlay(const SArgs& a, const SRow& R, SSm&
     if (R.h_lo + t + (int64_t)q * CT < h_reg_end) count(hreg[q], 1u, 0u);
   });
   for_hist([&](int32_t id, int64_t) { count(id, 1u, 0u); });
-  for_ids(a.prompt_ids, R.p_lo, R.p_hi, [&](int32_t id, int64_t) { count(id, 0u, 0x80000000u); });
-  const int32_t* st_cnt = reinterpret_cast<const int32_t*>(a.st_counts + R.row * a.st_cap);
-  for_ids(st_cnt, 0, R.st_n, [&](int32_t cvi, int64_t e) {
-    const uint32_t cv = (uint32_t)cvi;
-    count(st_row[e], cv & 0x7fffffffu, cv & 0x80000000u);
-  });
+  if constexpr (EXT) {
+    for_ids(a.prompt_ids, R.p_lo, R.p_hi, [&](int32_t id, int64_t) { count(id, 0u, 0x80000000u); });
+    // the state's ids and counts, requested together (an id read behind its count's arrival made every
+    // entry of a thread two round trips)
+    const uint32_t* st_cnt = a.st_counts + R.row * a.st_cap;
+    for (int e0 = t; e0 < R.st_n; e0 += IDU * CT) {
+      int32_t id[IDU];
+      uint32_t cv[IDU];
+#pragma unroll
+      for (int q = 0; q < IDU; ++q) {
+        const int e = e0 + q * CT < R.st_n ? e0 + q * CT : e0;
+        id[q] = st_row[e];
+        cv[q] = st_cnt[e];
+      }
+#pragma unroll
+      for (int q = 0; q < IDU; ++q)
+        if (e0 + q * CT < R.st_n) count(id[q], cv[q] & 0x7fffffffu, cv[q] & 0x80000000u);
+    }
+  }
   __syncthreads();
   return n_x;
 }
@@ -1289,14 +1305,14 @@ __device__ __forceinline__ int gp_draw(const SArgs& a, const SRow& R, SSm& s, fl
   return id;
 }
 
-// The general path rebuilds a chunk's penalty overlay for every re-read: the row's output history,
-// copied to LDS when the kernel starts, is grouped by the chunk its ids fall in, so that a rebuild
-// reads only its chunk's ids.  Every thread of the workgroup calls it.
+// Before the general path's re-reads of a whole row, each of which rebuilds a chunk's penalty overlay: the
+// row's output history to LDS, grouped by the chunk its ids fall in, so that a rebuild reads only its
+// chunk's ids.  Every thread of the workgroup calls it.
 template <class DT>
 __device__ __forceinline__ void stage_history(const SArgs& a, const SRow& R, SSm& s) {
   const int t = threadIdx.x;
   const int64_t nh = R.h_hi - R.h_lo;
-  if (s.hst_on) {
+  if (R.pen_on && nh > 0 && nh <= HSTAGE) {
     // the ids grouped by the chunk they fall in (a counting sort; the order inside a group does not
     // matter, its ids are counted by atomics); ids outside [0, V) are left out (the chunk kernel has
     // flagged them already)
@@ -1304,8 +1320,9 @@ __device__ __forceinline__ void stage_history(const SArgs& a, const SRow& R, SSm
     int32_t v[Q];
     static_for<Q>([&](auto I) {
       constexpr int q = decltype(I)::value;
-      v[q] = r_hstage[min(t + q * CT, (int)nh - 1)];
+      v[q] = a.prm.hist_ids[R.h_lo + min((int64_t)(t + q * CT), nh - 1)];
     });
+    if (t == 0) s.hst_on = 1;
     if (t <= R.P) s.hoff[t] = 0;
     __syncthreads();
     int cq[Q];
@@ -1889,26 +1906,6 @@ __device__ __forceinline__ void gen_c_item(const SArgs& a, SSm& s, int64_t row) 
   row_setup<DT, SEG>(a, row, 0, R);
   const int P = R.P;
   if (t == 0) s.hst_on = 0;
-  // before a pass over the whole row: the output history to LDS, grouped by chunk, for the overlay
-  // rebuilds (the draw's walk over one chunk reads its ids from memory)
-  auto history_to_lds = [&]() __attribute__((always_inline)) {
-    const int64_t nh = R.h_hi - R.h_lo;
-    if (R.pen_on && nh > 0 && nh <= HSTAGE) {
-      constexpr int Q = HSTAGE / CT;
-      int32_t v[Q];
-      static_for<Q>([&](auto I) {  // every load in flight before any is stored
-        constexpr int q = decltype(I)::value;
-        v[q] = a.prm.hist_ids[R.h_lo + min((int64_t)(t + q * CT), nh - 1)];
-      });
-      static_for<Q>([&](auto I) {
-        constexpr int q = decltype(I)::value;
-        if (t + q * CT < nh) r_hstage[t + q * CT] = v[q];
-      });
-      if (t == 0) s.hst_on = 1;
-    }
-    __syncthreads();
-    stage_history<DT>(a, R, s);
-  };
   __syncthreads();
   const uint64_t* rec = a.rec + (row * P) * (int64_t)REC_WORDS;
   const float m = d.m, lo = d.lo;
@@ -2071,7 +2068,7 @@ __device__ __forceinline__ void gen_c_item(const SArgs& a, SSm& s, int64_t row) 
               }
             } else {
               // one pass over the row: a comparison per value, masses only inside bucket bb
-              history_to_lds();
+              stage_history<DT>(a, R, s);
               for (int c = 0; c < P; ++c) {
                 for_chunk<DT, SEG>(a, R, s, c, [&](float z, int pos) __attribute__((always_inline)) {
                   if (z > -INFINITY && z >= lo && gp_dbucket(z, m) == bb) take(z, pos);
@@ -2111,7 +2108,7 @@ __device__ __forceinline__ void gen_c_item(const SArgs& a, SSm& s, int64_t row) 
     id = gp_draw<DT, SEG>(a, R, s, tau, m, d.u, &zid, true, last);
   } else {
     // the crossing sub-bucket did not fit the staging: the single-workgroup nucleus selection
-    history_to_lds();
+    stage_history<DT>(a, R, s);
     bool fused = gp_topp_fused<DT, SEG>(a, R, s, lo, m, (double)d.p, tau, last);
     if (!fused) {
       const uint32_t kk = gp_topp<DT, SEG>(a, R, s, lo, m, (double)d.p);
@@ -2207,7 +2204,7 @@ __global__ __launch_bounds__(CT, 1) void k_gen_c(SArgs a) {
 // ----------------------------------------------------------------------------------------------
 // The kernel: one workgroup per (row, chunk)
 // ----------------------------------------------------------------------------------------------
-template <class DT, bool SEG>
+template <class DT, bool SEG, bool EXT>
 __global__ __launch_bounds__(CT, 4) void k_stream(SArgs a) {
   __shared__ SSm s;
   const int t = threadIdx.x;
@@ -2227,8 +2224,8 @@ __global__ __launch_bounds__(CT, 4) void k_stream(SArgs a) {
   const void* dummy = a.rec;
   constexpr int HPT = 16;
   int32_t hreg[HPT];
-  const int nh = R.pen_on ? (int)min(R.h_hi - R.h_lo, (int64_t)HPT * CT) : 0;  // ids held in hreg
   {
+    const int nh = R.pen_on ? (int)min(R.h_hi - R.h_lo, (int64_t)HPT * CT) : 0;  // ids held in hreg
     const int32_t* hrow = nh > 0 ? a.prm.hist_ids + R.h_lo : static_cast<const int32_t*>(dummy);
     static_for<HPT>([&](auto Q) {
       constexpr int q = decltype(Q)::value;
@@ -2269,7 +2266,7 @@ __global__ __launch_bounds__(CT, 4) void k_stream(SArgs a) {
   const int nwords = (int)(((R.s1 - R.s0 + 2) * VEC + 31) >> 5);
   int n_x = 0;  // penalised extras
   uint32_t tfl = 0;
-  if (R.pen_on) n_x = build_overlay<HPT>(a, R, s, c, R.s0, R.s1, VEC, hreg, &tfl);
+  if (R.pen_on) n_x = build_overlay<HPT, EXT>(a, R, s, c, R.s0, R.s1, VEC, hreg, &tfl);
   if (tfl) atomicOr(&s.flags, tfl);
 
   // ---- one pass over the slots in arrival order: the penalised elements leave the registers for
@@ -2666,23 +2663,7 @@ __global__ __launch_bounds__(CT, 1) void k_resolve(SArgs a) {
   const int t = threadIdx.x;
   SRow R;
   row_setup<DT, SEG>(a, (int64_t)blockIdx.x, 0, R);
-  // the output history to LDS (all of a thread's loads in flight together) for the general path, which
-  // groups it by chunk if the row needs it
   if (t == 0) s.hst_on = 0;
-  const int64_t nh = R.h_hi - R.h_lo;
-  if (R.pen_on && nh > 0 && nh <= HSTAGE) {
-    constexpr int Q = HSTAGE / CT;
-    int32_t v[Q];
-    static_for<Q>([&](auto I) {
-      constexpr int q = decltype(I)::value;
-      v[q] = a.prm.hist_ids[R.h_lo + min((int64_t)(t + q * CT), nh - 1)];
-    });
-    static_for<Q>([&](auto I) {
-      constexpr int q = decltype(I)::value;
-      if (t + q * CT < nh) r_hstage[t + q * CT] = v[q];
-    });
-    if (t == 0) s.hst_on = 1;
-  }
   __syncthreads();
   resolve_row<DT, SEG>(a, R, s);
 }
@@ -2804,16 +2785,19 @@ albireo_status_t launch(const Request& q) {
   a.dq = reinterpret_cast<int32_t*>(q.ws + w.dq);
   void* args[] = {&a};
   const void *fc, *fr, *ga, *gb, *gs, *gc;
+  const bool ext = a.prompt_offsets || a.st_len;
 #define ALBIREO_STREAM_KERNELS(DT)                                                                  \
   if (q.shards) {                                                                                   \
-    fc = reinterpret_cast<const void*>(&k_stream<DT, true>);                                        \
+    fc = ext ? reinterpret_cast<const void*>(&k_stream<DT, true, true>)                             \
+             : reinterpret_cast<const void*>(&k_stream<DT, true, false>);                           \
     fr = reinterpret_cast<const void*>(&k_resolve<DT, true>);                                       \
     ga = reinterpret_cast<const void*>(&k_gen_a<DT, true>);                                         \
     gb = reinterpret_cast<const void*>(&k_gen_b<DT, true>);                                         \
     gs = reinterpret_cast<const void*>(&k_gen_s<DT, true>);                                         \
     gc = reinterpret_cast<const void*>(&k_gen_c<DT, true>);                                         \
   } else {                                                                                          \
-    fc = reinterpret_cast<const void*>(&k_stream<DT, false>);                                       \
+    fc = ext ? reinterpret_cast<const void*>(&k_stream<DT, false, true>)                            \
+             : reinterpret_cast<const void*>(&k_stream<DT, false, false>);                          \
     fr = reinterpret_cast<const void*>(&k_resolve<DT, false>);                                      \
     ga = reinterpret_cast<const void*>(&k_gen_a<DT, false>);                                        \
     gb = reinterpret_cast<const void*>(&k_gen_b<DT, false>);                                        \
