@@ -307,10 +307,13 @@ __device__ __forceinline__ void lse_add(float& m, float& s, float m2, float s2) 
   m = M;
 }
 
-// fixed-point mass of a kept value: 2^((z - m) L2E) in units of 2^-32
+// fixed-point mass of a kept value (z <= m): 2^((z - m) L2E) in units of 2^-32, rounded down.  Below 1 the
+// scaled weight is exact in fp32 and fits 32 bits; a conversion through double took a dozen half-rate
+// instructions of the re-reading passes' thirty per value.
 __device__ __forceinline__ uint64_t mass_of(float z, float m) {
   const float w = __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(z, m), L2E));
-  return (uint64_t)((double)w * FIX_SCALE);
+  const bool one = !(w < 1.0f);
+  return ((uint64_t)(one ? 1u : 0u) << 32) | (one ? 0u : (uint32_t)(w * 4294967296.0f));
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -1778,14 +1781,10 @@ __device__ __forceinline__ void gen_a_item(const SArgs& a, SSm& s, int64_t row, 
   const float m = d.m, lo = d.lo;
   const bool topp = d.topp;
   for_chunk_h<DT, SEG, 16>(a, R, s, c, hreg, [&](float z, int pos) __attribute__((always_inline)) {
-    if (z > -INFINITY && z >= lo) {
-      const uint64_t w = mass_of(z, m);
-      if (w) {
-        acc += w;
-        last = max(last, pos);
-        if (topp) atomicAdd(reinterpret_cast<unsigned long long*>(&h64[gp_dbucket(z, m)]), (unsigned long long)w);
-      }
-    }
+    const uint64_t w = z >= lo ? mass_of(z, m) : 0ull;  // 0 for -inf too
+    acc += w;
+    last = w ? max(last, pos) : last;
+    if (topp && w) atomicAdd(reinterpret_cast<unsigned long long*>(&h64[gp_dbucket(z, m)]), (unsigned long long)w);
   });
   acc = blk_sum_u64(acc, s);
   last = blk_max_i(last, s);
@@ -1820,24 +1819,22 @@ __device__ __forceinline__ void gen_b_item(const SArgs& a, SSm& s, int64_t row, 
   int last = -1;
   const float m = d.m, lo = d.lo;
   uint64_t* stg = a.stg + L * (int64_t)SSTRIDE;
+  const float bb_lo = (float)bb, bb_hi = bb == GDB - 1 ? INFINITY : (float)(bb + 1);
   uint64_t* sub = s.c.list;  // the crossing bucket's mass per sub-bucket
   for (int i = t; i < GDB; i += CT) sub[i] = 0;
   __syncthreads();
   for_chunk_h<DT, SEG, 16>(a, R, s, c, hreg, [&](float z, int pos) __attribute__((always_inline)) {
-    if (z > -INFINITY && z >= lo) {
-      const int b = gp_dbucket(z, m);
-      if (b < bb) {
-        const uint64_t w = mass_of(z, m);
-        if (w) {
-          acc += w;
-          last = max(last, pos);
-        }
-      } else if (b == bb) {
-        const int i = atomicAdd(&s.n_list, 1);
-        if (i < SCAP) stg[i] = ((uint64_t)f2key(z) << 32) | (uint32_t)pos;
-        const uint64_t w = mass_of(z, m);
-        if (w) atomicAdd(reinterpret_cast<unsigned long long*>(&sub[gp_dsub(z, m, bb)]), (unsigned long long)w);
-      }
+    // z in a bucket above bb (d < bb), in bb (bb <= d < bb + 1; the last bucket has no end), or neither
+    const float d = __fmul_rn(__fsub_rn(m, z), GD_SCALE);
+    const bool ok = z > -INFINITY && z >= lo;
+    const uint64_t w = ok && d < bb_lo ? mass_of(z, m) : 0ull;
+    acc += w;
+    last = w ? max(last, pos) : last;
+    if (ok && d >= bb_lo && d < bb_hi) {
+      const int i = atomicAdd(&s.n_list, 1);
+      if (i < SCAP) stg[i] = ((uint64_t)f2key(z) << 32) | (uint32_t)pos;
+      const uint64_t ws = mass_of(z, m);
+      if (ws) atomicAdd(reinterpret_cast<unsigned long long*>(&sub[gp_dsub(z, m, bb)]), (unsigned long long)ws);
     }
   });
   acc = blk_sum_u64(acc, s);
