@@ -3757,7 +3757,7 @@ albireo_status_t albireo_topk_topp(const float* logits, int64_t B, int64_t V, in
   if (make_geometry(B, V, ALBIREO_F32, G) != hipSuccess) return ALBIREO_E_LAUNCH;
   if (!G.ok) return ALBIREO_E_UNSUPPORTED;
   // Rows of more than one register chunk go to the chunk-parallel kernels of filter.hip (64 x 128256,
-  // top-k and top-p mixed: 419 us in the cooperative kernel, 54 us there).  Rows that fit one workgroup do so
+  // top-k and top-p mixed: 419 us in the cooperative kernel, 52 us there).  Rows that fit one workgroup do so
   // where top-p alone is given, which the one-workgroup kernel selects over re-reads of the row (32000
   // logits: 110-120 us against 30-34 us); where top-k or min-p is given the kept set may be a short
   // candidate list, which it resolves in one launch (top-k 40 of 8000 logits: 17 us against 28 us; of 32000:

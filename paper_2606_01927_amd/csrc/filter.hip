@@ -15,8 +15,8 @@
 // Bound: HBM for the first read and the written probabilities (the second and third read come from the
 // caches); what is left is the four launches' ramps.  Splitting each row over its chunks is what the
 // one-launch kernels cannot do without waiting for each other.  64 rows of 128256 logits, top-k and top-p
-// mixed: 419-429 us in one cooperative launch of two workgroups per row, 54 us here (13 us the
-// histograms, 17 the staging, 13 the cuts, 12 the writing).
+// mixed: 419-429 us in one cooperative launch of two workgroups per row, 52 us here (13 us the
+// histograms, 17 the staging, 11 the cuts, 12 the writing).
 #include <hip/hip_runtime.h>
 
 #include <float.h>
@@ -24,6 +24,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
 #include <utility>
 
 #include "albireo.h"
@@ -595,27 +596,34 @@ struct RowSrc {  // f(z) for every value of the row
   }
 };
 
-// select_key for n <= ST staged values: thread i compares value i with every other; two barriers where the
-// byte rounds take twelve
-template <class W>
+// select_key for n <= ST staged values: thread i compares value i with every other (waves without a value
+// sit the loop out); two barriers where the byte rounds take twelve.  COUNT: every value weighs 1 and the
+// sums are 32-bit.
+template <bool COUNT, class W>
 __device__ __forceinline__ uint32_t select_few(SolveLds& s, int n, float lo, double target, double above, W&& weight) {
   const int t = threadIdx.x;
   const uint32_t mine = t < n ? s.keys[t] : 0u;
   const float z = key2f(mine);
   const bool in = t < n && z > -INFINITY && z >= lo;
-  const uint32_t wt = in ? (uint32_t)weight(z) : 0u;
   __syncthreads();
-  s.wt[t] = wt;
+  if constexpr (!COUNT) s.wt[t] = in ? (uint32_t)weight(z) : 0u;
   if (t == 0) s.hit = 0;
   __syncthreads();
-  uint64_t gt = 0, eq = 0;
+  if (wave_id() * 64 < n) {
+    using Sum = std::conditional_t<COUNT, uint32_t, uint64_t>;
+    Sum gt = 0, ge = 0;
+    const uint32_t klo = COUNT ? f2key(lo) : 0u;  // (weights below lo are 0)
 #pragma unroll 8
-  for (int i = 0; i < n; ++i) {
-    const uint32_t k = s.keys[i], w = s.wt[i];
-    gt += k > mine ? w : 0u;
-    eq += k == mine ? w : 0u;
+    for (int i = 0; i < n; ++i) {
+      const uint32_t k = s.keys[i];
+      uint32_t w = 1u;
+      if constexpr (!COUNT) w = s.wt[i];
+      if constexpr (COUNT) w = k >= klo ? 1u : 0u;
+      gt += k > mine ? w : 0u;
+      ge += k >= mine ? w : 0u;
+    }
+    if (in && ge > gt && above + (double)gt < target && above + (double)ge >= target) s.hit = (int32_t)mine;
   }
-  if (in && eq > 0 && above + (double)gt < target && above + (double)(gt + eq) >= target) s.hit = (int32_t)mine;
   __syncthreads();
   return (uint32_t)s.hit;
 }
@@ -719,7 +727,10 @@ __global__ __launch_bounds__(ST, 2) void k_filter_solve(FArgs a) {
       __syncthreads();
     }
     tau = X.tau_m;
-    auto one = [](float) __attribute__((always_inline)) -> uint64_t { return 1ull; };
+    struct One {
+      __device__ __forceinline__ uint64_t operator()(float) const { return 1ull; }
+    };
+    const One one{};
     const float gref = gref_of(m);
     auto mass = [&](float z) __attribute__((always_inline)) -> uint64_t { return fix_weight(z, gref); };
     // both filters over a source that holds every value they can keep
@@ -769,7 +780,8 @@ __global__ __launch_bounds__(ST, 2) void k_filter_solve(FArgs a) {
       __syncthreads();
       const StagedSrc src{s.keys, n};
       auto sel = [&](float lo, double target, double ab, auto&& w) __attribute__((always_inline)) {
-        return n <= ST ? select_few(s, n, lo, target, ab, w) : select_key(src, s, lo, target, ab, w);
+        constexpr bool COUNT = std::is_same_v<std::decay_t<decltype(w)>, One>;
+        return n <= ST ? select_few<COUNT>(s, n, lo, target, ab, w) : select_key(src, s, lo, target, ab, w);
       };
       if (kind == K_ALL) {
         select_all(src, sel);
