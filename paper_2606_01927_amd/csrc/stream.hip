@@ -2153,7 +2153,9 @@ constexpr int GEN_ROWS = 512;
 
 template <class DT, bool SEG, int K>
 __device__ __forceinline__ void gen_chunks(const SArgs& a, SSm& s) {
-  const int64_t n = (int64_t)a.dq[0] * a.P;
+  const int nd = sload(a.dq);  // written by the launch before: a scalar load, and nothing else without rows
+  if (nd == 0) return;
+  const int64_t n = (int64_t)nd * a.P;
   for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
     const int64_t row = a.dq[2 + item / a.P];
     const int c = (int)(item % a.P);
@@ -2183,7 +2185,8 @@ __global__ __launch_bounds__(CT) void k_gen_s(SArgs a) {
 template <class DT, bool SEG>
 __global__ __launch_bounds__(CT, 1) void k_gen_c(SArgs a) {
   __shared__ SSm s;
-  const int n = a.dq[0];
+  const int n = sload(a.dq);
+  if (n == 0) return;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     gen_c_item<DT, SEG>(a, s, a.dq[2 + i]);
     __syncthreads();
