@@ -2153,7 +2153,10 @@ constexpr int GEN_ROWS = 512;
 
 template <class DT, bool SEG, int K>
 __device__ __forceinline__ void gen_chunks(const SArgs& a, SSm& s) {
-  const int nd = sload(a.dq);  // written by the launch before: a scalar load, and nothing else without rows
+  // written by the launch before: a scalar load, and nothing else without rows (512 x 152064 fp32 without a
+  // deferred row, beside the call before the general path's last changes: 69.4 against 69.0 us with the vector
+  // load, 69.7 against 69.7 with this one)
+  const int nd = sload(a.dq);
   if (nd == 0) return;
   const int64_t n = (int64_t)nd * a.P;
   for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
