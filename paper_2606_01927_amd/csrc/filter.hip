@@ -45,7 +45,7 @@ constexpr int CAP = 4096;         // values staged per row
 constexpr int MAXPC = 64;         // chunks per row (one per lane)
 constexpr int ST = 512;           // threads of a row's solving workgroup
 constexpr int REC = 8;            // 64-bit words per chunk record
-constexpr float MAX_M = 262144.0f;  // above, 32 z is no longer a small exact integer: selected over memory
+constexpr float MAX_M = 1e36f;    // above, 32 z may overflow: selected over memory
 constexpr double FIX44 = 17592186044416.0;
 
 // What decides a row's cut (record word 5 of chunk 0, with the bucket above it).
@@ -147,10 +147,13 @@ __device__ __forceinline__ float qfloor(float z) { return floorf(z * BSCALE); }
 // bucket of z below the bucket number qtop of a maximum; the last one takes everything further down
 __device__ __forceinline__ int bucket(float qtop, float z) { return (int)fminf(qtop - qfloor(z), (float)(NB - 1)); }
 
-// weight of z against the maximum m, below 1 (the reference is just above m)
-__device__ __forceinline__ float gref_of(float m) { return __fmul_rn(m, L2E) + fmaxf(fabsf(m) * 1e-6f, 1e-6f); }
-__device__ __forceinline__ uint32_t fix_weight(float z, float gref) {
-  return (uint32_t)(__builtin_amdgcn_exp2f(__builtin_fmaf(z, L2E, -gref)) * 4294967296.0f);
+// The smallest z in the buckets up to b below qtop: bucket(z) <= b is 32 z >= qtop - b exactly, but past 2^24
+// that difference is no float, so it is taken in double and rounded up.  (Bucket numbers near the maximum
+// differ exactly at any magnitude; further away any rounding stays past the last bucket.)
+__device__ __forceinline__ float bucket_edge(float qtop, int b) {
+  const double x = ((double)qtop - (double)b) / (double)BSCALE;
+  const float f = (float)x;
+  return (double)f < x ? key2f(f2key(f) + 1u) : f;
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -204,7 +207,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_hist(FArgs a) {
   const Hist ht = hist_of(R);
   const bool finite = cm > -INFINITY && cm < INFINITY;
   if (ht != H_NONE && finite) {
-    const float qtop = qfloor(cm), gref = gref_of(cm);
+    const float qtop = qfloor(cm);
     // Values below low move no cut: those under a bound of the chunk's k-th largest value (at most the row's),
     // those more than log min-p below the chunk's maximum, and those whose weight is 0 in units of 2^-32.
     // The LDS adds bound this pass (64 rows of 128256: 20 us with all of them), and these are most of them.
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_hist(FArgs a) {
     }
     auto add = [&](float z) __attribute__((always_inline)) {
       if (z >= low) {
-        const uint32_t u = ht == H_MASS ? fix_weight(z, gref) : 1u;
+        const uint64_t u = ht == H_MASS ? mass_of(z, cm) : 1ull;
         atomicAdd((unsigned long long*)&h[bucket(qtop, z)], (unsigned long long)u);
       }
     };
@@ -348,8 +351,8 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
       const float cm = __uint_as_float((uint32_t)a.rec[(row * a.P + i) * REC]);
       // a chunk whose maximum is far below, or which has no finite value, falls into the last bucket whole
       coff[i] = (int)fminf(qtop - qfloor(cm), (float)NB);
-      // the chunk's weights are against its own reference
-      cscale[i] = ht == H_MASS ? __builtin_amdgcn_exp2f(gref_of(cm) - gref_of(m)) : 1.0f;
+      // the chunk's weights are against its own maximum
+      cscale[i] = ht == H_MASS ? __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(cm, m), L2E)) : 1.0f;
     }
     __syncthreads();
     // row bucket b of a chunk whose maximum lies off buckets below the row's: its bucket b - off; the last
@@ -446,11 +449,11 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
   float zmin = INFINITY;
   uint32_t* list = a.lists + L * LC;
   // sure: z >= zs, kept whatever the cut in the bucket; staged: zl <= z < zs0, the bucket's values (K_ALL: all
-  // from the bucket up).  bucket(z) <= b is 32 z >= qtop - b, exactly, as 32 z and the bucket numbers are exact.
+  // from the bucket up)
   float zs0 = -FLT_MAX, zl = INFINITY;  // K_NONE stages nothing
   if (kind != K_NONE) {
-    zs0 = kind == K_ALL ? INFINITY : (qtop - (float)(bb - 1)) / BSCALE;
-    zl = bb < NB - 1 ? (qtop - (float)bb) / BSCALE : -FLT_MAX;
+    zs0 = kind == K_ALL ? INFINITY : bucket_edge(qtop, bb - 1);
+    zl = bb < NB - 1 ? bucket_edge(qtop, bb) : -FLT_MAX;
   }
   const float zs = fmaxf(zs0, lo);
   auto classify = [&](float z, bool& sure, bool& st) __attribute__((always_inline)) {
@@ -538,7 +541,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
 // ----------------------------------------------------------------------------------------------
 struct SolveLds {
   uint32_t keys[CAP];
-  uint32_t wt[ST];
+  uint64_t wt[ST];
   uint64_t h[256];
   uint64_t red[ST / 64];
   int32_t off[MAXPC + 1];
@@ -606,7 +609,7 @@ __device__ __forceinline__ uint32_t select_few(SolveLds& s, int n, float lo, dou
   const float z = key2f(mine);
   const bool in = t < n && z > -INFINITY && z >= lo;
   __syncthreads();
-  if constexpr (!COUNT) s.wt[t] = in ? (uint32_t)weight(z) : 0u;
+  if constexpr (!COUNT) s.wt[t] = in ? weight(z) : 0ull;
   if (t == 0) s.hit = 0;
   __syncthreads();
   if (wave_id() * 64 < n) {
@@ -616,11 +619,11 @@ __device__ __forceinline__ uint32_t select_few(SolveLds& s, int n, float lo, dou
 #pragma unroll 8
     for (int i = 0; i < n; ++i) {
       const uint32_t k = s.keys[i];
-      uint32_t w = 1u;
-      if constexpr (!COUNT) w = s.wt[i];
+      Sum w;
       if constexpr (COUNT) w = k >= klo ? 1u : 0u;
-      gt += k > mine ? w : 0u;
-      ge += k >= mine ? w : 0u;
+      else w = s.wt[i];
+      gt += k > mine ? w : Sum(0);
+      ge += k >= mine ? w : Sum(0);
     }
     if (in && ge > gt && above + (double)gt < target && above + (double)ge >= target) s.hit = (int32_t)mine;
   }
@@ -731,8 +734,7 @@ __global__ __launch_bounds__(ST, 2) void k_filter_solve(FArgs a) {
       __device__ __forceinline__ uint64_t operator()(float) const { return 1ull; }
     };
     const One one{};
-    const float gref = gref_of(m);
-    auto mass = [&](float z) __attribute__((always_inline)) -> uint64_t { return fix_weight(z, gref); };
+    auto mass = [&](float z) __attribute__((always_inline)) -> uint64_t { return mass_of(z, m); };
     // both filters over a source that holds every value they can keep
     auto select_all = [&](const auto& src, auto&& sel) __attribute__((always_inline)) {
       if (R.kon) {
@@ -789,7 +791,7 @@ __global__ __launch_bounds__(ST, 2) void k_filter_solve(FArgs a) {
         const uint32_t kk = sel(-INFINITY, (double)R.k - above, 0.0, one);
         if (kk) tau = fmaxf(tau, key2f(kk));
       } else {
-        // the chunks' weights are in units of 2^-32 of the row's reference, like these
+        // the chunks' weights are in units of 2^-32 against the row's maximum, like these
         uint32_t kk = sel(-INFINITY, (double)R.p * total, above, mass);
         if (kk) {
           tau = fmaxf(tau, key2f(kk));

@@ -174,3 +174,31 @@ def test_empty_and_bad_rows():
     fl = _run(x, *_params(combos))
     empty, bad = alb.FLAG_EMPTY, alb.FLAG_BAD_INPUT
     assert fl[0] & empty and fl[1] & bad and fl[2] & bad and not (fl[3:] & (empty | bad)).any()
+
+
+@pytest.mark.parametrize("V", [20003, 90000])
+def test_maxima_of_any_magnitude(V):
+    """Maxima from 2^18 to 1e30 in both signs, the values below them spaced by the type's own steps: weights and
+    bucket edges hold at any magnitude.  V on both sides of one register chunk (top-p alone in the first)."""
+    rng = np.random.default_rng(11)
+    rows, combos = [], []
+    for combo in [(1.0, 0, 0.5, 0.0), (1.0, 0, 0.9, 0.0), (1.0, 100, 0.8, 0.0), (1.0, 30, 1.0, 0.0), (1.0, 0, 0.7, 1e-4)]:
+        if V < ONE_WG and (combo[1] or combo[3]):
+            continue
+        for m in (2.6e5, 3e5, 6e5, 1.1e6, 1e7, -1e7, 2.5e7, 4e7, 1e8, -1e8, 1e30, -1e30):
+            x = (m - abs(m) * rng.uniform(0.01, 1, V)).astype(np.float32)
+            at, top = rng.permutation(V), np.float32(m)
+            x[at[0]] = top
+            step, used = float(top) - float(np.nextafter(top, np.float32(-np.inf))), 1
+            for k in range(1, 200):  # k steps below the maximum: the more values, the less each weighs
+                n = int(min(math.ceil(math.exp(min(k * step, 50.0)) / 2), 1500))
+                if used + n > 6000 or n == 1500:
+                    break
+                x[at[used:used + n]] = np.float32(float(top) - k * step)
+                used += n
+            rows.append(x)
+            combos.append(combo)
+    for scale in (100.0, 400.0):  # ordinary logits at a temperature next to greedy
+        rows.append(rng.normal(0, scale, V).astype(np.float32))
+        combos.append((2e-5, 0, 0.9, 0.0))
+    _run(np.stack(rows).astype(np.float32), *_params(combos))
