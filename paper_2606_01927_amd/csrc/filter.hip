@@ -323,7 +323,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
   __shared__ int n_list;
   __shared__ int wcnt[NWV];
   __shared__ uint32_t wmin[NWV];
-  __shared__ float cscale[MAXPC];
+  __shared__ double cscale[MAXPC];
   __shared__ int coff[MAXPC];
   const int t = threadIdx.x;
   const int64_t L = blockIdx.x, row = L / a.P;
@@ -351,8 +351,10 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
       const float cm = __uint_as_float((uint32_t)a.rec[(row * a.P + i) * REC]);
       // a chunk whose maximum is far below, or which has no finite value, falls into the last bucket whole
       coff[i] = (int)fminf(qtop - qfloor(cm), (float)NB);
-      // the chunk's weights are against its own maximum
-      cscale[i] = ht == H_MASS ? __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(cm, m), L2E)) : 1.0f;
+      // the chunk's weights are against its own maximum: their factor in double, so that the merge adds
+      // nothing to the weights' own rounding but one unit of 2^-32 per bucket (a chunk without a finite
+      // value has empty buckets: exp2 of -inf is 0)
+      cscale[i] = ht == H_MASS ? exp2(((double)cm - (double)m) * (double)L2E) : 1.0;
     }
     __syncthreads();
     // row bucket b of a chunk whose maximum lies off buckets below the row's: its bucket b - off; the last
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = min(i0 + u, a.P - 1), off = coff[i];
-        const double sc = (double)cscale[i];
+        const double sc = cscale[i];
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
           const int b = t * BPT + k;
