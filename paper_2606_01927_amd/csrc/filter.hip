@@ -466,7 +466,6 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
   static_assert(4 * CJ < 63, "a thread's values do not fit the staging mask");
 #pragma unroll
   for (int j = 0; j < CJ; ++j) {
-    float w[4];
     uint32_t any = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -479,8 +478,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
     }
     if (__ballot(any != 0)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (any >> e) & 1u ? __expf(d[j].v[e] - m) : 0.0f;
-      acc += (double)((w[0] + w[1]) + (w[2] + w[3]));
+      for (int e = 0; e < 4; ++e) acc += (double)((any >> e) & 1u ? __expf(d[j].v[e] - m) : 0.0f);
       cnt += __popc(any);
     }
   }
