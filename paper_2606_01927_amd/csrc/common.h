@@ -75,15 +75,6 @@ __device__ __forceinline__ uint64_t cand_key(float z, int pos) {
 __device__ __forceinline__ float cand_z(uint64_t k) { return key2f((uint32_t)(k >> 32)); }
 __device__ __forceinline__ int cand_pos(uint64_t k) { return (int)(~(uint32_t)k); }
 __device__ __forceinline__ uint64_t fixmass(float w) { return (uint64_t)((double)w * FIX_SCALE); }
-// fixed-point mass of a value z <= m: 2^((z - m) L2E) in units of 2^-32, rounded down; from the difference,
-// so that it holds at any magnitude of m.  Below 1 the
-// scaled weight is exact in fp32 and fits 32 bits; a conversion through double took a dozen half-rate
-// instructions of the re-reading passes' thirty per value.
-__device__ __forceinline__ uint64_t mass_of(float z, float m) {
-  const float w = __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(z, m), L2E));
-  const bool one = !(w < 1.0f);
-  return ((uint64_t)(one ? 1u : 0u) << 32) | (one ? 0u : (uint32_t)(w * 4294967296.0f));
-}
 
 template <class T>
 __device__ __forceinline__ T ld_agent(const T* p) {

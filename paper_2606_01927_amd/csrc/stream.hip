@@ -307,6 +307,15 @@ __device__ __forceinline__ void lse_add(float& m, float& s, float m2, float s2) 
   m = M;
 }
 
+// fixed-point mass of a kept value (z <= m): 2^((z - m) L2E) in units of 2^-32, rounded down.  Below 1 the
+// scaled weight is exact in fp32 and fits 32 bits; a conversion through double took a dozen half-rate
+// instructions of the re-reading passes' thirty per value.
+__device__ __forceinline__ uint64_t mass_of(float z, float m) {
+  const float w = __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(z, m), L2E));
+  const bool one = !(w < 1.0f);
+  return ((uint64_t)(one ? 1u : 0u) << 32) | (one ? 0u : (uint32_t)(w * 4294967296.0f));
+}
+
 // ----------------------------------------------------------------------------------------------
 // Chunk records: five 64-bit words (a 32-bit field and a float each)
 // ----------------------------------------------------------------------------------------------
