@@ -402,10 +402,10 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
     rest = wave_sum_u64(rest);
     if (lane_id() == 63) wtot[wave_id()] = rest;
     __syncthreads();
-    if (t == CT - 1) {
-      hv[BPT - 1] = 0;
-      for (int w = 0; w < NWV; ++w) hv[BPT - 1] += wtot[w];
-    }
+    uint64_t last = 0;  // the row's last bucket
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) last += wtot[w];
+    if (t == CT - 1) hv[BPT - 1] = last;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < BPT; ++k) sum += hv[k];
@@ -416,6 +416,7 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
     for (int w = 0; w < wave_id(); ++w) ex += wtot[w];
 #pragma unroll
     for (int w = 0; w < NWV; ++w) total += wtot[w];
+    const uint64_t body = total - last;
     // the bucket where the cumulative reaches the target, or the one of the min-p cut
     const bool by_cut = ht == H_COUNT && !R.kon;
     const double target = R.kon ? (double)R.k : (double)R.p * (double)total;
@@ -441,7 +442,15 @@ __global__ __launch_bounds__(CT, 4) void k_filter_stage(FArgs a) {
     } else if (!R.topp_on) {
       kind = bb < NB ? K_COUNT : K_NONE;  // fewer than k finite values: top-k keeps them all
     } else {
-      kind = bb < NB && cx.upto <= (uint64_t)CAP ? K_ALL : K_SLOW;
+      // Every value down to the crossing bucket, or to the last bucket but one: what lies in the last is 32
+      // below the maximum, weighs less than 2^-46 and cannot move a top-p cut (which lies where the weights do),
+      // nor is it kept, as top-p < 1 keeps no more than it needs.  So a row with fewer than k finite values
+      // (a mask), where nothing crosses, or with its k-th value that far down needs no selection over memory:
+      // 64 x 128256, top-k 40 and top-p 0.9, 20 ids unmasked: 219 us over memory, 46 us staged; values of scale
+      // 3e5: 345 us and 45 us.
+      const uint64_t n_all = bb < NB - 1 ? cx.upto : body;
+      bb = min(bb, NB - 2);
+      kind = n_all <= (uint64_t)CAP ? K_ALL : K_SLOW;
     }
   } else if (ht != H_NONE) {
     kind = K_SLOW;

@@ -202,3 +202,22 @@ def test_maxima_of_any_magnitude(V):
         rows.append(rng.normal(0, scale, V).astype(np.float32))
         combos.append((2e-5, 0, 0.9, 0.0))
     _run(np.stack(rows).astype(np.float32), *_params(combos))
+
+
+def test_cuts_in_the_last_bucket():
+    """Two filters whose count or min-p cut lies 32 and more below the maximum, or is never reached: fewer finite
+    values than k, steep rows, tiny min-p.  The staged list then ends above the last bucket, and holds at most
+    4096 values or leaves the row to the selection over memory."""
+    rng = np.random.default_rng(12)
+    rows, combos = [], []
+    for V_fin in (1, 20, 39, 1000, 4096, 4097, 20000):
+        x = np.full(90000, -np.inf)
+        x[rng.permutation(90000)[:V_fin]] = rng.normal(0, 2, V_fin)
+        for k, p in ((40, 0.9), (V_fin + 1, 0.999), (30000, 1 - 2.0 ** -24)):
+            rows.append(x)
+            combos.append((1.0, k, p, 0.0))
+    for spread in (31.9, 33.0, 200.0, 3e5):
+        for combo in ((1.0, 40, 0.9, 0.0), (1.0, 9000, 0.99, 0.0), (1.0, 0, 0.9, 1e-20), (1.0, 80000, 0.5, 1e-30)):
+            rows.append(-rng.random(90000) ** 0.5 * spread)
+            combos.append(combo)
+    _run(np.stack(rows).astype(np.float32), *_params(combos))
