@@ -3757,13 +3757,16 @@ albireo_status_t albireo_topk_topp(const float* logits, int64_t B, int64_t V, in
   if (make_geometry(B, V, ALBIREO_F32, G) != hipSuccess) return ALBIREO_E_LAUNCH;
   if (!G.ok) return ALBIREO_E_UNSUPPORTED;
   // Rows of more than one register chunk go to the chunk-parallel kernels of filter.hip (64 x 128256,
-  // top-k and top-p mixed: 419 us in the cooperative kernel, 52 us there).  Rows that fit one workgroup do so
-  // where top-p alone is given, which the one-workgroup kernel selects over re-reads of the row (32000
-  // logits: 110-120 us against 30-34 us); where top-k or min-p is given the kept set may be a short
-  // candidate list, which it resolves in one launch (top-k 40 of 8000 logits: 17 us against 28 us; of 32000:
-  // 24-26 against 33-36), and the host cannot see the values.  A workspace below their need (a caller that
-  // sized it for a smaller call) leaves the call to the register-resident kernels.
-  const bool by_chunks = G.P > 1 || (params && params->top_p && !params->top_k && !params->min_p);
+  // top-k and top-p mixed: 419 us in the cooperative kernel, 52 us there).  Shorter rows do so where top-p
+  // alone is given and the row is longer than the one-workgroup kernel's candidate list, past which that
+  // kernel selects over re-reads of the row (1 to 256 rows of 8000 logits: 42-44 us Zipf-like, 73-100 flat,
+  // 15-43 with one token holding the mass, against 21-27 us; of 32000: 51-121, 92-125, 22-118 against 24-30).
+  // Up to 2048 logits every row fits the list, and rows of few kept tokens take one launch of 13-17 us where
+  // four take 19-24; past it such rows lose up to 6 us in batches of 16 and less.  Where top-k or min-p is
+  // given the kept set may be a short list at any length (top-k 40 of 8000 logits: 17 us against 28 us; of
+  // 32000: 24-26 against 33-36), and the host cannot see the values.  A workspace below the need of filter.hip
+  // (a caller that sized it for a smaller call) leaves the call to the register-resident kernels.
+  const bool by_chunks = G.P > 1 || (V > LCAP && params && params->top_p && !params->top_k && !params->min_p);
   const size_t fneed = by_chunks ? albireo_filter::workspace_bytes(B, V) : 0;
   if (fneed > 0 && check_ws(workspace, workspace_bytes, fneed) == ALBIREO_OK)
     return albireo_filter::launch(logits, B, V, ld, params, out_probs, out_threshold, out_kept, out_log_norm, out_flags,

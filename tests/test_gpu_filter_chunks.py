@@ -221,3 +221,13 @@ def test_cuts_in_the_last_bucket():
             rows.append(-rng.random(90000) ** 0.5 * spread)
             combos.append(combo)
     _run(np.stack(rows).astype(np.float32), *_params(combos))
+
+
+@pytest.mark.parametrize("V", [2048, 2049])
+def test_top_p_alone_at_the_candidate_list(V):
+    """The longest row that the one-workgroup kernel keeps (its list holds 2048), and the next."""
+    rng = np.random.default_rng(V)
+    combos = [(t, 0, p, 0.0) for t in (0.0, 0.6, 1.0) for p in (0.0, 0.3, 0.9, 0.999, 1.0)]
+    x = rng.normal(0, 2, (len(combos), V)).astype(np.float32)
+    x[::2, 7] += 12.0
+    _run(x, *_params(combos))
