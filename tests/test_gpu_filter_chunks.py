@@ -231,3 +231,38 @@ def test_top_p_alone_at_the_candidate_list(V):
     x = rng.normal(0, 2, (len(combos), V)).astype(np.float32)
     x[::2, 7] += 12.0
     _run(x, *_params(combos))
+
+
+@pytest.mark.parametrize("V", [30000, 90000])
+def test_smaller_workspace(V):
+    """A workspace below the chunk-parallel kernels' need but enough for the register-resident ones (none at all
+    where a row takes one workgroup): the same distribution from those."""
+    import ctypes
+
+    import torch
+
+    import paper_2606_01927_amd as alb
+
+    B = 6
+    rng = np.random.default_rng(V)
+    x = torch.from_numpy(rng.normal(0, 2.5, (B, V)).astype(np.float32)).cuda()
+    T, _, p, _ = _params([(t, 0, p, 0.0) for t, p in ((1.0, 0.9), (0.7, 0.5), (0.5, 0.99), (1.0, 1.0), (0.0, 0.5), (2.0, 0.3))])
+    # top-p in the middle of the interval its group falls into
+    p = np.array([_reference(x[i].cpu().numpy(), T[i], 0, p[i], 0.0)[2] for i in range(B)], np.float32)
+    rows = alb.SamplingParams(temperature=torch.from_numpy(T).cuda(), top_p=torch.from_numpy(p).cuda())
+    prm = alb._params(rows, x.device)
+    full = int(alb._lib.albireo_workspace_size(B, V, alb.F32, 0))
+    buf = torch.zeros(full + 256, dtype=torch.uint8, device="cuda")
+    base = buf.data_ptr() + (-buf.data_ptr()) % 256
+    got = []
+    for ws, n in ((base, full), (base, full * 3 // 4) if V > ONE_WG else (None, 0)):
+        o = [torch.empty((B, V), device="cuda")] + [torch.empty(B, dtype=d, device="cuda") for d in
+                                                    (torch.float32, torch.int32, torch.float32, torch.int32)]
+        rc = alb._lib.albireo_topk_topp(x.data_ptr(), B, V, V, ctypes.byref(prm), *[t.data_ptr() for t in o], ws, n, None)
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert int(buf.count_nonzero()) == 0
+        got.append([t.cpu().numpy() for t in o])
+    (pr, thr, kept, ln, fl), (pr2, thr2, kept2, ln2, fl2) = got
+    assert np.array_equal(thr, thr2) and np.array_equal(kept, kept2) and np.array_equal(fl, fl2)
+    assert np.abs(pr - pr2).max() <= 1e-5 and np.abs(ln - ln2).max() <= 1e-5
