@@ -758,6 +758,14 @@ __device__ void write_top_n(const OutArgs& a, Smem& s, const RowCtx& X, int64_t 
 }
 
 constexpr double WFIX40 = 1099511627776.0;  // 2^40
+constexpr double FIX44 = 17592186044416.0;  // 2^44
+
+// A weight of at most 1 in units of 1 / scale, rounded down, and at least one unit for any positive weight:
+// the draw at u = 0 is the first token of positive probability, however small.
+__device__ __forceinline__ uint64_t fix_positive(float w, double scale) {
+  const uint64_t u = (uint64_t)((double)w * scale);
+  return u == 0 && w > 0.0f ? 1ull : u;
+}
 
 // ----------------------------------------------------------------------------------------------
 // Selections by digits: every thread holds up to EPT entries (a 32-bit key and a weight) in registers;
@@ -919,7 +927,7 @@ __device__ __forceinline__ void write_top_small(const OutArgs& a, Smem& s, const
 static_assert(3 * LCAP * 4 / 8 >= LCAP, "top-n staging below the candidate list");
 
 // A sampled row whose candidate list holds more than SMALL_LIST entries: top-k, min-p, top-p and the
-// draw by digit selections over the list (masses exp(z - m) in units of 2^-40).
+// draw by digit selections over the list (masses exp(z - m) in units of 2^-40, at least one).
 __device__ __noinline__ Resolution resolve_mid(const OutArgs a, Smem& s, const RowState R, const RowCtx X,
                                                Resolution res) {
   const int n = X.n_list;
@@ -932,7 +940,7 @@ __device__ __noinline__ Resolution resolve_mid(const OutArgs a, Smem& s, const R
     const uint64_t k = i < n ? s.sk[i] : 0ull;
     key[q] = (uint32_t)(k >> 32);
     pos[q] = (uint32_t)cand_pos(k);
-    w[q] = i < n ? (uint64_t)((double)__expf(cand_z(k) - m) * WFIX40) : 0ull;
+    w[q] = i < n ? fix_positive(__expf(cand_z(k) - m), WFIX40) : 0ull;
   }
   float tau2 = X.tau_m;
   uint32_t kk;
@@ -1825,7 +1833,6 @@ __device__ __noinline__ Resolution resolve_general(const OutArgs a, Smem& s, con
 // ----------------------------------------------------------------------------------------------
 constexpr int GSL = 4;                              // slots of a thread per group
 constexpr int NGRP = (JMAX + GSL - 1) / GSL;        // groups of a row
-constexpr double FIX44 = 17592186044416.0;          // 2^44
 static_assert(GSL * NT <= SD_B, "a group's slots exceed the scan array");
 static_assert(sizeof(Smem::scode) >= 2 * SD_B * sizeof(uint64_t), "group scan arrays do not fit");
 
@@ -2050,7 +2057,7 @@ __device__ __noinline__ Resolution resolve_open(const OutArgs a, Smem& s, const 
       } else {
         in = z >= tau;
       }
-      if (in) atomicAdd((unsigned long long*)&G.gx[group_of(pos)], (unsigned long long)((double)weight(z) * FIX44));
+      if (in) atomicAdd((unsigned long long*)&G.gx[group_of(pos)], (unsigned long long)fix_positive(weight(z), FIX44));
     })
   };
   if (a.n_top > 0) {
@@ -2086,7 +2093,7 @@ __device__ __noinline__ Resolution resolve_open(const OutArgs a, Smem& s, const 
       const float z = key2f(key[q]);
       if (i < n && z >= tau)
         atomicAdd((unsigned long long*)&G.gx[group_of((int)(uint32_t)s.sk[i])],
-                  (unsigned long long)((double)weight(z) * FIX44));
+                  (unsigned long long)fix_positive(weight(z), FIX44));
     }
     __syncthreads();
   }
@@ -2139,7 +2146,7 @@ __device__ __noinline__ Resolution resolve_open(const OutArgs a, Smem& s, const 
     FOR_EXTRAS(s, n_ext, {
       const float z = canon(x, r);
       if (z >= tau && group_of(pos) == gi)
-        atomicAdd((unsigned long long*)&fx[(pos - b0) / VEC], (unsigned long long)((double)weight(z) * FIX44));
+        atomicAdd((unsigned long long*)&fx[(pos - b0) / VEC], (unsigned long long)fix_positive(weight(z), FIX44));
     })
     if (t == 0) {
       s.bc_i[0] = INT32_MAX;

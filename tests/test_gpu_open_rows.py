@@ -105,3 +105,46 @@ def test_ties_and_masks(kind, oracle_mod):
         out = _run(w, 0, n_top)
         w.n_top = n_top
         _check(oracle_mod.sample(w), out, n_top)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["list", "head", "penalised"])
+def test_uniform_zero_draws_the_smallest_weight(where, dtype):
+    """At u = 0 the draw is the first token of positive probability, whatever its weight (2^-40 to 2^-52 of the
+    largest here: the oracle's margins would leave such a row out): the first entry of a candidate list, of the
+    unaligned head, and a penalised one."""
+    import torch
+
+    import paper_2606_01927_amd as alb
+
+    V, es = 20011, 2 if dtype == "bf16" else 4
+    drops = (28.5, 32.0, 36.0)
+    B = len(drops)
+    rng = np.random.default_rng(4)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.from_numpy(rng.normal(0, 0.5, (B, V)).astype(np.float32)).to(dt)
+    first = 0 if where != "penalised" else 7  # 7: past the head
+    x[:, :first] = -float("inf")
+    if where == "list":  # 300 finite values, one to a thread, all of them kept by top-k
+        keep = torch.arange(300) * (16 // es)
+        x[:, ~torch.isin(torch.arange(V), keep)] = -float("inf")
+    if where == "head":  # nothing else in the head
+        x[:, 1:16] = -float("inf")
+    x[:, 400] = 8.0
+    x[:, first] = torch.tensor([8.0 - d for d in drops]).to(dt)
+    ld = V + (16 // es - V % (16 // es))
+    buf = torch.zeros(B * ld + 16, dtype=dt, device="cuda")
+    off = 1 if where == "head" else 0
+    rows = buf[off:off + B * ld].view(B, ld)
+    rows[:, :V] = x.cuda()
+    p = alb.SamplingParams(temperature=torch.ones(B, device="cuda"))
+    if where == "list":
+        p.top_k = torch.full((B,), 300, dtype=torch.int32, device="cuda")
+    if where == "penalised":  # a penalty of 0: the token takes the path of the penalised ones
+        p.hist_offsets = torch.arange(B + 1, dtype=torch.int64, device="cuda")
+        p.hist_ids = torch.full((B,), first, dtype=torch.int32, device="cuda")
+        p.presence_penalty = torch.zeros(B, device="cuda")
+    u = torch.zeros(B, device="cuda")
+    assert alb.sample_route(B, V, dt, p) == alb.ROUTE_ONE_WORKGROUP
+    ids = alb.sample(rows[:, :V], u, p, V=V)[0].cpu().numpy()
+    assert (ids == first).all(), ids
