@@ -148,3 +148,29 @@ def test_uniform_zero_draws_the_smallest_weight(where, dtype):
     assert alb.sample_route(B, V, dt, p) == alb.ROUTE_ONE_WORKGROUP
     ids = alb.sample(rows[:, :V], u, p, V=V)[0].cpu().numpy()
     assert (ids == first).all(), ids
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 20011), ("bf16", 128256)])
+@pytest.mark.parametrize("allowed", [1, 3, 64, 128, 129, 511, 2000, 2500])
+def test_masked_rows(allowed, dtype, V, oracle_mod):
+    """Rows of a few finite values, from one to past the candidate list: threads and waves without any, more
+    top-n slots than values, and the normaliser evaluated before or beside the counting (with and without
+    top-p alone)."""
+    B = 4
+    for kind in ("plain", "nucleus", "minp", "topk", "greedy"):
+        w = _rows(dtype, V, B, "plain" if kind == "greedy" else kind, allowed, 0)
+        rng = np.random.default_rng(allowed)
+        neg = np.float32(-np.inf) if dtype == "f32" else np.uint16(0xff80)
+        x = np.array(w.logits[:, :V], copy=True)
+        for i in range(B):
+            at = rng.permutation(V)[:allowed] if i else np.arange(allowed)  # row 0: all in the first threads
+            row = np.full(V, neg)
+            row[at] = x[i, at]
+            x[i] = row
+        w.logits, w.ld = x, V
+        if kind == "greedy":
+            w.temperature = np.zeros(B, np.float32)
+        for n_top in (0, 5, 32):
+            out = _run(w, 0, n_top)
+            w.n_top = n_top
+            _check(oracle_mod.sample(w), out, n_top)
