@@ -337,7 +337,9 @@ __global__ __launch_bounds__(APP_NT) void k_state_append(albireo_penalty_state_t
   }
 }
 
-// k_state_init_bitmap's dynamic LDS passes 64 KB: allowed once per device.
+// k_state_init_bitmap's dynamic LDS passes 64 KB: allowed once per device.  Where it is refused, or the device
+// index is past the table, the sort kernel takes the call (the refusal is no error of the call's: it is
+// cleared ahead of the launch's own check).
 constexpr int MAX_DEV = 64;
 bool big_lds_allowed() {
   static std::mutex mu;
@@ -349,6 +351,7 @@ bool big_lds_allowed() {
     const int most = (int)(MAXS * 8 + BM_MAXV / 32 * 6);
     done[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_state_init_bitmap),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess;
+    if (!done[dev]) (void)hipGetLastError();
   }
   return done[dev];
 }
@@ -374,10 +377,9 @@ albireo_status_t albireo_penalty_state_init(const albireo_penalty_state_t* state
   if (prompt_offsets && (prompt_len < 0 || (prompt_len > 0 && !prompt_ids))) return ALBIREO_E_INVALID;
   if (out_offsets && (out_len < 0 || (out_len > 0 && !out_ids))) return ALBIREO_E_INVALID;
   if (B == 0) return ALBIREO_OK;
-  if (V <= BM_MAXV) {
+  if (V <= BM_MAXV && big_lds_allowed()) {
     const int nwords = (int)((V + 127) / 128 * 4);
     const size_t lds = (size_t)MAXS * 8 + (size_t)nwords * 6;
-    if (lds > 64 * 1024 && !big_lds_allowed()) return ALBIREO_E_LAUNCH;
     hipLaunchKernelGGL(k_state_init_bitmap, dim3((unsigned)B), dim3(INIT_NT), lds, stream, *state, V, nwords,
                        prompt_offsets, prompt_ids, prompt_len, out_offsets, out_ids, out_len);
     return hipGetLastError() == hipSuccess ? ALBIREO_OK : ALBIREO_E_LAUNCH;
