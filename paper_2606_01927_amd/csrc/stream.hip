@@ -2153,12 +2153,7 @@ constexpr int GEN_ROWS = 512;
 
 template <class DT, bool SEG, int K>
 __device__ __forceinline__ void gen_chunks(const SArgs& a, SSm& s) {
-  // written by the launch before: a scalar load, and nothing else without rows (512 x 152064 fp32 without a
-  // deferred row, beside the call before the general path's last changes: 69.4 against 69.0 us with the vector
-  // load, 69.7 against 69.7 with this one)
-  const int nd = sload(a.dq);
-  if (nd == 0) return;
-  const int64_t n = (int64_t)nd * a.P;
+  const int64_t n = (int64_t)a.dq[0] * a.P;
   for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
     const int64_t row = a.dq[2 + item / a.P];
     const int c = (int)(item % a.P);
@@ -2188,8 +2183,7 @@ __global__ __launch_bounds__(CT) void k_gen_s(SArgs a) {
 template <class DT, bool SEG>
 __global__ __launch_bounds__(CT, 1) void k_gen_c(SArgs a) {
   __shared__ SSm s;
-  const int n = sload(a.dq);
-  if (n == 0) return;
+  const int n = a.dq[0];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     gen_c_item<DT, SEG>(a, s, a.dq[2 + i]);
     __syncthreads();
