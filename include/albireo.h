@@ -35,7 +35,8 @@
  *   - Results are bit-identical from run to run (no floating-point atomics), and identical for a row
  *     whether it is sampled alone or inside any batch as long as the row starts at the same address
  *     modulo 16 bytes (always the case when ld * element size is a multiple of 16 and the buffers are
- *     16-byte aligned): the reduction order is fixed by V, dtype and that alignment.
+ *     16-byte aligned): the reduction order is fixed by V, dtype and that alignment (for albireo_topk_topp
+ *     also by which filters are given, and by a workspace smaller than albireo_workspace_size).
  */
 #ifndef ALBIREO_H
 #define ALBIREO_H
@@ -75,10 +76,13 @@ typedef enum {
 #define ALBIREO_FLAG_TIMEOUT 32u  /* a bounded wait gave up (a value another workgroup or wave
                                      publishes never became visible within the spin limit); the
                                      row's other outputs are unspecified.  The waits: between the
-                                     workgroups of a wide row (albireo_topk_topp, and the cooperative
-                                     sampling route ALBIREO_ROUTE_COOPERATIVE), and, in the
-                                     one-workgroup kernel, between the waves of a penalised row for
-                                     its presence bitmap.  The streaming route never waits.       */
+                                     workgroups of a wide row on the cooperative kernels (the sampling
+                                     route ALBIREO_ROUTE_COOPERATIVE, and albireo_topk_topp where its
+                                     workspace is below albireo_workspace_size or the row is past the
+                                     streaming kernels' width), and, in the one-workgroup kernel,
+                                     between the waves of a penalised row for its presence bitmap.
+                                     The streaming route, and albireo_topk_topp's launches per row
+                                     chunk, never wait.                                           */
 
 #define ALBIREO_MAX_TOP_N 32
 #define ALBIREO_MAX_UNIQUE_HISTORY 2048
@@ -237,6 +241,9 @@ albireo_status_t albireo_apply_penalties(const void* logits, albireo_dtype_t dty
 
 /*
  * Apply steps 3-5 to already-penalised fp32 logits and report the filtered distribution.
+ *   workspace      albireo_workspace_size bytes.  A smaller one that still holds what the register-resident
+ *                  kernels need (nothing for rows of one register chunk) is taken too: those kernels then
+ *                  resolve the call, with the same kept sets and sums in another order
  *   params         [host] uses temperature, top_k, top_p, min_p; penalty members are ignored
  *   out_probs      [B, V] fp32 (row stride V) renormalised probabilities over the kept set S, 0 outside
  *                  S, or NULL.  A greedy row keeps only its argmax (probability 1).

@@ -1826,12 +1826,13 @@ __device__ __noinline__ Resolution resolve_general(const OutArgs a, Smem& s, con
 // rest in double); LDS sums of single values are integers.
 //
 // Bound: VALU on the row's one CU, about 15 instructions per value and pass at 4 cycles per wave
-// instruction (an exponential four times that).  The passes are free of branches, so that the eight
-// values of a slot overlap: with the LDS add under a test per value, a 128256-logit row spent 57-87 us
-// in the histogram.  The row is read again (256 KB, from the caches) rather than kept in the caller's
-// registers, which cost every other row of the kernel 2-4 % in spilled scalars.  64 rows of 128256 bf16
-// logits: nucleus rows 230-257 us with selections and a draw over six and more passes through memory and
-// double conversions, 64-75 us here; plain rows 105 -> 38 us.
+// instruction (an exponential four times that): the two waves of a SIMD keep it 58 % busy on Zipf-like rows
+// (64 x 128256 bf16, T = 0.6) and 71 % on masked ones, and the LDS is taken for a tenth of the time.  The passes
+// are free of branches, so that the eight values of a slot overlap: with the LDS add under a test per value,
+// a 128256-logit row spent 57-87 us in the histogram.  The row is read again (256 KB, from the caches) rather
+// than kept in the caller's registers, which cost every other row of the kernel 2-4 % in spilled scalars.
+// 64 rows of 128256 bf16 logits: nucleus rows 220-257 us with selections and a draw over six and more passes
+// through memory and double conversions, 57-66 us here; plain rows 105 -> 38 us.
 // ----------------------------------------------------------------------------------------------
 constexpr int GSL = 4;                              // slots of a thread per group
 constexpr int NGRP = (JMAX + GSL - 1) / GSL;        // groups of a row

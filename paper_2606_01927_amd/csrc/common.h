@@ -1,7 +1,7 @@
 // common.h -- device helpers shared by the sampling kernels of this library (one copy per
 // translation unit; everything here has internal linkage through the enclosing anonymous namespace).
 //
-// Included by albireo.hip and stream.hip inside `namespace {`.
+// Included by albireo.hip, stream.hip, filter.hip and penalties.hip inside `namespace {`.
 #pragma once
 constexpr uint32_t SPIN_LIMIT = 1u << 24;
 constexpr double FIX_SCALE = 4294967296.0;  // fixed-point scale of the general path's masses

@@ -40,8 +40,8 @@ __device__ __forceinline__ void csr_row(const int64_t* off, int64_t len, int64_t
 // takes every occurrence's id, a prefix count over its words numbers the distinct ids in ascending
 // order, and every occurrence then counts itself at its id's number.  Nothing is sorted.
 //
-// Bound: the latency of the row's two round trips to memory and eight barriers, about 4096 LDS atomics
-// on the way; one workgroup per CU (up to 136 KB of LDS).  64 rows of 1000 + 3000 ids, V = 128256:
+// Bound: the latency of the row's two round trips to memory and five barriers, two LDS atomics per
+// occurrence on the way (one on the bitmap, one on its entry); one workgroup per CU (up to 136 KB of LDS).  64 rows of 1000 + 3000 ids, V = 128256:
 // 50.9 us with the bitonic sort below (78 barrier-separated stages over 4096 keys), 8.9 us here.
 constexpr int64_t BM_MAXV = 393216;       // 48 KB of bitmap and 24 KB of word prefixes beside 64 KB of entries
 

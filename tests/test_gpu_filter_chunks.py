@@ -1,7 +1,7 @@
 """albireo_topk_topp through the chunk-parallel kernels: row lengths at the edges of a chunk (19456 values),
 of a 16-byte slot and of one register chunk, strided rows at any 4-byte boundary, every combination of the
 filters, and the rows that leave the histogram's cut to a selection over memory (one value many times, kept
-sets past the staging, maxima past 2^18).  Against plain torch in 64 bits on the fp32 processed logits:
+sets past the staging), and maxima of any magnitude.  Against plain torch in 64 bits on the fp32 processed logits:
 threshold, kept count and flags exactly (top-p is moved to the middle of the interval its group falls into),
 probabilities and log-normaliser within 1e-5: a weight 2^a, |a| <= 24, carries a relative error of at most
 24 * 2^-24 ln 2 + 2^-22 = 1.2e-6, and so does a sum of them.  Where a group's interval is narrower than that error
